@@ -172,6 +172,41 @@ def test_build_graph_small_alpha_variants():
         assert (g.cpu().numpy() == ref).all()
 
 
+def _repair_points(which):
+    r = np.random.default_rng(17)
+    if which == "equal points":
+        # groups of equal points larger than the candidate lists: most
+        # bridges need a full scan, and all of them want the same few nodes
+        base = r.integers(0, 40, size=(900, 8))
+        base[r.permutation(900)[:600]] = base[:3].repeat(200, 0)
+        return base, 24, 12, 1.2
+    if which == "islands":
+        # far groups no larger than the lists, wider than one staged block of
+        # dimensions; R at its largest
+        cen = r.integers(0, 4000, size=(60, 136))
+        return cen[r.integers(0, 60, 1300)] + r.integers(-3, 4, size=(1300, 136)), 64, 64, 1.0
+    if which == "line":
+        # points on a line, one candidate each: chains, and full scans for the rest
+        return r.permutation(701)[:, None] * np.array([[1, 0, 0]]), 1, 3, 1.2
+    # "ring": two candidates each, so labels travel along one long chain
+    a = np.arange(1024) * (2 * np.pi / 1024)
+    base = np.rint(np.stack([np.cos(a), np.sin(a), 0 * a, 0 * a], 1) * 4096)
+    return base[r.permutation(1024)], 2, 4, 1.0
+
+
+@pytest.mark.parametrize("which", ["equal points", "islands", "line", "ring"])
+def test_build_graph_repair_bit_exact(which):
+    base, K, R, alpha = _repair_points(which)
+    base = np.ascontiguousarray(base, np.float32)
+    say("case: repair, %s" % which)
+    ref, med, nf, nr, _, _ = oracle.build_graph(base, K, R, alpha)
+    assert nf > 0 or which == "ring"
+    g, gm, (gf, gr) = _ann().ann_build_graph(_dev(base), K, R, alpha)
+    torch.cuda.synchronize()
+    assert gm == med and (gf, gr) == (nf, nr)
+    assert (g.cpu().numpy() == ref).all()
+
+
 def test_build_graph_partitioned_bit_exact():
     # candidates among the members of each point's home group (k-means
     # clusters, a second group for a third of the points, repeats, a home
