@@ -651,8 +651,15 @@ __global__ void __launch_bounds__(64) select_kernel(const uint64_t *buf, const i
 // are then mostly seen early, its threshold is tight for the rest of the
 // pass, and few columns reach the append path.  Only the visiting order
 // changes; the selection is exact in any order.
+// A cluster-ordered pass takes all columns in one slice: a second slice would
+// hold none of a row's own group, start with an open threshold and let in
+// about K (1 + ln(n / K)) strangers per row (300,000 x 128, K = 128: 129 ms in
+// two slices, 43 ms in one).  With fewer rows the one slice leaves most of the
+// GPU idle while each wavefront sorts its 64 rows: 30,000 x 128 21.4 ms in
+// cluster order against 16.4 ms in id order over 17 slices, 50,000 x 128
+// 20.9 against 31.4 ms.
 constexpr int kClusters = 256;
-constexpr int64_t kClusterMinN = 65536;   // below this the pass is short anyway
+constexpr int64_t kClusterMinN = 40960;
 
 // the sample rows (int8) and their norms
 __global__ void sample_rows_kernel(const int8_t *x8, const int32_t *xn, int64_t n, int dim,
@@ -755,7 +762,7 @@ struct Plan {
     int64_t slice_len;
 };
 
-Plan plan(int64_t n, int64_t rows, int K)
+Plan plan(int64_t n, int64_t rows, int K, bool one_slice)
 {
     Plan p{};
     p.Kp = K + 1;          // room for the row's own column
@@ -770,7 +777,7 @@ Plan plan(int64_t n, int64_t rows, int K)
     const int64_t by_merge = kMaxMerged / p.Kp > 1 ? kMaxMerged / p.Kp : 1;
     if (s > by_len) s = by_len;
     if (s > by_merge) s = by_merge;
-    if (s < 1) s = 1;
+    if (s < 1 || one_slice) s = 1;
     p.slice_len = ((n + s - 1) / s + kCols - 1) / kCols * kCols;
     p.slices = (int)((n + p.slice_len - 1) / p.slice_len);
     if (p.slices < 1) p.slices = 1;
@@ -790,7 +797,8 @@ size_t cluster_ws(int64_t n, int dim)
 
 size_t workspace(int64_t n, int64_t rows, int dim, int K)
 {
-    const Plan p = plan(n, rows, K);
+    // the caller's queries may or may not be the base rows: room for both orders
+    const Plan p = plan(n, rows, K, false);
     size_t b = round_up((size_t)rows * p.slices * p.cap * 8, 256);
     b += round_up((size_t)rows * p.slices * 4, 256);
     b += round_up((size_t)n * dim, 256) + round_up((size_t)n * 4, 256);
@@ -869,7 +877,9 @@ ann_status knn_run(const float *base, int64_t n, int dim, const float *queries, 
     }
     if (force_engine == 1 && !use_int) return fail(ANN_EINVAL, "int8 engine needs integer data in [0,255]");
     if (use_int) {
-        const i8::Plan pl = i8::plan(n, rows, K);
+        const bool clustered = queries == base && self_col == nullptr &&
+                               i8::cluster_order(n, rows) && n <= 0x7FFFFFFF;
+        const i8::Plan pl = i8::plan(n, rows, K, clustered);
         i8::Args a{};
         a.buf = reinterpret_cast<uint64_t *>(p);
         p += round_up((size_t)rows * pl.slices * pl.cap * 8, 256);
@@ -886,8 +896,7 @@ ann_status knn_run(const float *base, int64_t n, int dim, const float *queries, 
         const int32_t *row_map = nullptr;
         a.col_id = nullptr;
         a.start_tile = nullptr;
-        if (queries == base && self_col == nullptr && i8::cluster_order(n, rows) &&
-            n <= 0x7FFFFFFF) {
+        if (clustered) {
             // all pairs: rows and columns in the order of their nearest sample
             // row, ids reported through the permutation
             const int C = i8::kClusters;
