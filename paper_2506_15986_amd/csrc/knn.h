@@ -17,7 +17,8 @@ struct KnnArgs {
     int64_t rows;
     int K;
     int exclude_self;
-    const int32_t *self_col;    // column excluded for query row g (null: column g)
+    const int32_t *self_col;    // column excluded for query row q (null: column q)
+    const int32_t *row_list;    // query row of row g of a launch (null: row g)
     knn::Ent *buf;
     int cap;
     int32_t *out_ids;

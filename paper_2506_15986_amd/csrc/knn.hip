@@ -9,10 +9,17 @@
 //   * FP64 engine: any data; d2 = sum_j (x_j - y_j)^2 in FP64.  On data held
 //     on a dyadic grid (values m * 2^-G with 2G + log2(d (2B)^2) <= 53) every
 //     partial sum is exact, so the result equals the FP64 sum in any order.
+//     It computes the distances of a shortlist only (knn_f16.h); the plain
+//     all-columns form below takes the rows whose shortlist cannot be told
+//     apart, and data that is not finite.
 // Both give the exact top K by (d2, id).
+#include <cmath>
+
 #include "common.h"
+#include "internal.h"
 #include "knn.h"
 #include "knn_core.h"
+#include "knn_f16.h"
 
 namespace ann {
 namespace {
@@ -88,36 +95,45 @@ __device__ inline void merge_full_rows(RowState &rs, Ent *buf, int64_t row0, int
     }
 }
 
-__device__ inline void write_rows(const RowState &rs, const Ent *buf, int64_t row0, int64_t rows,
-                                  int cap, int K, bool int_keys, int32_t *out_ids, float *out_f,
-                                  double *out_d)
+// query row of row g of the launch
+__device__ inline int64_t query_row(const KnnArgs &a, int64_t g)
 {
+    return a.row_list ? (int64_t)a.row_list[g] : g;
+}
+
+__device__ inline void write_rows(const RowState &rs, const KnnArgs &a, int64_t row0)
+{
+    const Ent *buf = a.buf;
+    const int64_t rows = a.rows;
+    const int cap = a.cap, K = a.K;
     const int w = threadIdx.x >> 6;
     const int lane = __lane_id();
     for (int r = w * knn::kRowsPerWave; r < (w + 1) * knn::kRowsPerWave; ++r) {
         int64_t g = row0 + r;
         if (g >= rows) break;
         int c = rs.cnt[r];
+        const int64_t q = query_row(a, g);
         for (int t = lane; t < K; t += 64) {
             int32_t id = -1;
             double v = __longlong_as_double(0x7ff0000000000000ll);
             if (t < c) {
                 Ent e = buf[g * cap + t];
                 id = (int32_t)e.id;
-                v = int_keys ? (double)e.k : knn::value_of(e.k);
+                v = knn::value_of(e.k);
             }
-            out_ids[g * K + t] = id;
-            if (out_f) out_f[g * K + t] = (float)v;
-            if (out_d) out_d[g * K + t] = v;
+            a.out_ids[q * K + t] = id;
+            if (a.out_f) a.out_f[q * K + t] = (float)v;
+            if (a.out_d) a.out_d[q * K + t] = v;
         }
     }
 }
 
-// base column that query row g must skip (-1: none)
+// base column that row g of the launch must skip (-1: none)
 __device__ inline int64_t self_column(const KnnArgs &a, int64_t g)
 {
     if (!a.exclude_self || g >= a.rows) return -1;
-    return a.self_col ? (int64_t)a.self_col[g] : g;
+    const int64_t q = query_row(a, g);
+    return a.self_col ? (int64_t)a.self_col[q] : q;
 }
 
 // ---------------------------------------------------------------- FP64 engine
@@ -154,7 +170,9 @@ __global__ void __launch_bounds__(256) knn_f64_kernel(KnnArgs a)
             for (int e = t; e < knn::kRows * F_DK; e += 256) {
                 int r = e / F_DK, j = e % F_DK;
                 int64_t g = row0 + r;
-                As[r][j] = (g < a.rows && dk + j < a.dim) ? a.queries[g * a.dim + dk + j] : 0.f;
+                As[r][j] = (g < a.rows && dk + j < a.dim)
+                               ? a.queries[query_row(a, g) * a.dim + dk + j]
+                               : 0.f;
             }
             for (int e = t; e < F_BN * F_DK; e += 256) {
                 int c = e / F_DK, j = e % F_DK;
@@ -194,7 +212,7 @@ __global__ void __launch_bounds__(256) knn_f64_kernel(KnnArgs a)
         merge_full_rows(rs, a.buf, row0, a.rows, a.cap, a.K, F_BN, scratch, false);
     }
     merge_full_rows(rs, a.buf, row0, a.rows, a.cap, a.K, F_BN, scratch, true);
-    write_rows(rs, a.buf, row0, a.rows, a.cap, a.K, false, a.out_ids, a.out_f, a.out_d);
+    write_rows(rs, a, row0);
 }
 
 // ---------------------------------------------------------------- int8 MFMA engine
@@ -830,11 +848,19 @@ size_t knn_cap(int K)
     return c;
 }
 
+// row buffers of the plain FP64 engine
+static size_t f64_buffer(int64_t rows, int K)
+{
+    return round_up((size_t)rows * knn_cap(K) * sizeof(Ent), 256);
+}
+
 size_t knn_workspace(int64_t n, int64_t rows, int dim, int K)
 {
-    const size_t f64 = round_up((size_t)rows * knn_cap(K) * sizeof(Ent), 256) + 256;
+    const size_t f64 = f64_buffer(rows, K);
     const size_t i8b = i8::workspace(n, rows, dim, K);
-    return (f64 > i8b ? f64 : i8b) + 256;
+    const size_t f16b = f16::buffer_bytes(n, rows, K, device_cus());
+    const size_t real = (f64 > f16b ? f64 : f16b) + f16::operand_bytes(n, rows, dim) + 256;
+    return (real > i8b ? real : i8b) + 256;
 }
 
 ann_status data_is_uint8(const float *x, int64_t count, int *flag_dev, bool *result, hipStream_t st)
@@ -851,6 +877,204 @@ ann_status data_is_uint8(const float *x, int64_t count, int *flag_dev, bool *res
     *result = (h == 0);
     return ANN_OK;
 }
+
+namespace {
+
+ann_status run_f64(const KnnArgs &a, hipStream_t st)
+{
+    const size_t lds = 4 * (size_t)a.cap * sizeof(Ent);
+    ANN_HIP(hipFuncSetAttribute((const void *)knn_f64_kernel,
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    hipLaunchKernelGGL(knn_f64_kernel, dim3((unsigned)((a.rows + knn::kRows - 1) / knn::kRows)),
+                       dim3(256), lds, st, a);
+    ANN_LAUNCHED();
+    return ANN_OK;
+}
+
+__global__ void set_words_kernel(uint32_t *p, int count)
+{
+    if ((int)threadIdx.x < count) p[threadIdx.x] = 0u;
+}
+
+// Real-valued data: the FP16 shortlist, its second level for the rows it
+// leaves, the plain engine for what that leaves.  Synchronises.
+ann_status run_f16(KnnArgs f, int *flag, unsigned char *p, hipStream_t st)
+{
+    const int64_t n = f.n, rows = f.rows;
+    const int dim = f.dim, dp = f16::padded(dim), cus = device_cus();
+    uint32_t *bits = reinterpret_cast<uint32_t *>(flag) + 1;
+    int32_t *todo_n = reinterpret_cast<int32_t *>(flag) + 2;      // one count per level
+    Carve cv{p};
+    const size_t fb = f64_buffer(rows, f.K), hb = f16::buffer_bytes(n, rows, f.K, cus);
+    unsigned char *buffers = cv.take<unsigned char>(fb > hb ? fb : hb);
+    _Float16 *bh = cv.take<_Float16>((size_t)n * dp), *bl = cv.take<_Float16>((size_t)n * dp);
+    _Float16 *qh = cv.take<_Float16>((size_t)rows * dp), *ql = cv.take<_Float16>((size_t)rows * dp);
+    float *bV = cv.take<float>((size_t)n), *bE = cv.take<float>((size_t)n);
+    float *qV = cv.take<float>((size_t)rows), *qE = cv.take<float>((size_t)rows);
+    float *centre = cv.take<float>((size_t)dim);
+    float *first = cv.take<float>((size_t)rows);
+    _Float16 *sh = cv.take<_Float16>((size_t)f16::kMaxSample * dp);
+    _Float16 *sl = cv.take<_Float16>((size_t)f16::kMaxSample * dp);
+    float *sV = cv.take<float>((size_t)f16::kMaxSample), *sE = cv.take<float>((size_t)f16::kMaxSample);
+    int32_t *todo[2] = {cv.take<int32_t>((size_t)rows), cv.take<int32_t>((size_t)rows)};
+    hipLaunchKernelGGL(set_words_kernel, dim3(1), dim3(64), 0, st, bits, 3);
+    ANN_LAUNCHED();
+    hipLaunchKernelGGL(f16::centre_kernel, dim3((unsigned)((dim + 63) / 64)), dim3(1024), 0, st, f.base,
+                       n, dim, centre);
+    ANN_LAUNCHED();
+    const bool same = f.queries == f.base && rows == n;
+    auto spread = [&](const float *x, int64_t m) {
+        const int64_t b = (m + 3) / 4;
+        hipLaunchKernelGGL(f16::spread_kernel, dim3((unsigned)(b < 2048 ? b : 2048)), dim3(256), 0, st, x,
+                           m, dim, centre, bits);
+    };
+    spread(f.base, n);
+    ANN_LAUNCHED();
+    if (!same) {
+        spread(f.queries, rows);
+        ANN_LAUNCHED();
+    }
+    const bool grouped = same && f.self_col == nullptr && n >= f16::kGroupedMinN;
+    int32_t *perm = nullptr;       // the rows in group order
+    int32_t left = (int32_t)rows;
+    for (int level = 0; level < 2 && left > 0; ++level) {
+        // level 0 takes every row, level 1 the rows listed in todo[0]
+        const f16::Coef co = f16::coef(dim, level == 1);
+        const int32_t *list = level ? todo[0] : nullptr;
+        const bool shared = same && level == 0;
+        auto convert = [&](const float *x, int64_t m, const int32_t *which, _Float16 *h, _Float16 *l,
+                           float *V, float *E) {
+            const dim3 grid((unsigned)((m + 3) / 4));
+            if (level)
+                hipLaunchKernelGGL(f16::convert_kernel<true>, grid, dim3(256), 0, st, x, m, dim, dp,
+                                   centre, bits, which, co, h, l, V, E);
+            else
+                hipLaunchKernelGGL(f16::convert_kernel<false>, grid, dim3(256), 0, st, x, m, dim, dp,
+                                   centre, bits, which, co, h, l, V, E);
+        };
+        const int32_t *start_col = nullptr;
+        if (level == 0 && grouped) {
+            // level 0 leaves the second parts' arrays and the rows' norms free
+            convert(f.base, n, nullptr, bl, bl, qV, qE);
+            ANN_LAUNCHED();
+            const int64_t blocks = (n + f16::kRowsWG - 1) / f16::kRowsWG;
+            int32_t *group = cv.take<int32_t>((size_t)n);
+            perm = cv.take<int32_t>((size_t)n);
+            // the sample rows use the (other) sample's memory
+            int32_t *hist = cv.take<int32_t>((size_t)f16::kGroups + 1);
+            int32_t *gstart = cv.take<int32_t>((size_t)f16::kGroups + 1);
+            int32_t *scol = cv.take<int32_t>((size_t)blocks);
+            hipLaunchKernelGGL(f16::sample_kernel, dim3(f16::kGroups), dim3(64), 0, st, bl, qV, n,
+                               f16::groups_of(n), dp, sh, sV);
+            ANN_LAUNCHED();
+            hipLaunchKernelGGL(set_words_kernel, dim3(1), dim3(f16::kGroups), 0, st,
+                               reinterpret_cast<uint32_t *>(hist), f16::kGroups);
+            ANN_LAUNCHED();
+            hipLaunchKernelGGL(f16::nearest_sample_kernel, dim3((unsigned)((n + 63) / 64)), dim3(256), 0,
+                               st, bl, n, dp, sh, sV, group, hist);
+            ANN_LAUNCHED();
+            hipLaunchKernelGGL(i8::group_starts_kernel, dim3(1), dim3(64), 0, st, hist, f16::kGroups,
+                               gstart, hist);
+            ANN_LAUNCHED();
+            hipLaunchKernelGGL(i8::place_rows_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
+                               group, n, hist, perm);
+            ANN_LAUNCHED();
+            hipLaunchKernelGGL(f16::permute_kernel, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, st, bl, qV,
+                               qE, perm, n, dp, bh, bV, bE);
+            ANN_LAUNCHED();
+            hipLaunchKernelGGL(f16::start_kernel, dim3((unsigned)((blocks + 255) / 256)), dim3(256), 0, st,
+                               group, perm, gstart, n, blocks, scol);
+            ANN_LAUNCHED();
+            start_col = scol;
+        } else {
+            convert(f.base, n, nullptr, bh, bl, bV, bE);
+            ANN_LAUNCHED();
+        }
+        if (!shared) {
+            convert(f.queries, left, list, qh, ql, qV, qE);
+            ANN_LAUNCHED();
+        }
+        // fewer rows may take more slices, as long as their buffers fit
+        const f16::Plan all = f16::plan(n, rows, f.K, cus, 0, false);
+        const f16::Plan pl = level     ? f16::plan(n, left, f.K, cus, rows * all.slices / left, false)
+                             : grouped ? f16::plan(n, rows, f.K, cus, 0, true)
+                                       : all;
+        f16::Args a{};
+        a.bh = bh;
+        a.bl = bl;
+        a.qh = shared ? bh : qh;
+        a.ql = ql;
+        a.bV = bV;
+        a.bE = bE;
+        a.qV = shared ? bV : qV;
+        a.qE = shared ? bE : qE;
+        a.n = n;
+        a.rows = left;
+        a.dpad = dp;
+        a.K = f.exclude_self ? pl.Kp : f.K;
+        a.keep = pl.keep;
+        a.slices = pl.slices;
+        a.slice_len = pl.slice_len;
+        a.start = start_col;
+        a.buf = reinterpret_cast<uint64_t *>(buffers);
+        a.cnt = reinterpret_cast<int32_t *>(buffers + round_up((size_t)left * pl.slices * pl.cap * 8, 256));
+        ann_status s = ANN_OK;
+        if (pl.S) {
+            float *est = reinterpret_cast<float *>(buffers);
+            s = level ? f16::first_thresholds<true>(a, pl.S, est, first, sh, sl, sV, sE, st)
+                      : f16::first_thresholds<false>(a, pl.S, est, first, sh, sl, sV, sE, st);
+            if (s != ANN_OK) return s;
+            a.first = first;
+        }
+        s = level ? f16::launch_tiles<true>(a, pl.cap, st) : f16::launch_tiles<false>(a, pl.cap, st);
+        if (s != ANN_OK) return s;
+        f16::FinalArgs fa{};
+        fa.base = f.base;
+        fa.queries = f.queries;
+        fa.rows = left;
+        fa.dim = dim;
+        fa.row_list = level ? list : perm;
+        fa.col_id = level ? nullptr : perm;
+        fa.qE = a.qE;
+        fa.bE = bE;
+        fa.bits = bits;
+        fa.buf = a.buf;
+        fa.cnt = a.cnt;
+        fa.slices = pl.slices;
+        fa.cap = pl.cap;
+        fa.K = f.K;
+        fa.Kp = a.K;
+        fa.most = pl.most;
+        fa.sort = pl.sort;
+        fa.vec4 = dim % 4 == 0 && aligned(f.base, 16) && aligned(f.queries, 16);
+        fa.exclude = f.exclude_self;
+        fa.self_col = f.self_col;
+        fa.out_ids = f.out_ids;
+        fa.out_f = f.out_f;
+        fa.out_d = f.out_d;
+        fa.todo = todo[level];
+        fa.todo_n = todo_n + level;
+        const size_t lds = f16::final_words(pl.most, pl.sort) + (size_t)pl.sort * 4;
+        ANN_HIP(hipFuncSetAttribute((const void *)f16::final_kernel,
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+        hipLaunchKernelGGL(f16::final_kernel, dim3((unsigned)left), dim3(64), lds, st, fa);
+        ANN_LAUNCHED();
+        uint32_t h[3];
+        ANN_HIP(hipMemcpyAsync(h, bits, sizeof(h), hipMemcpyDeviceToHost, st));
+        ANN_HIP(hipStreamSynchronize(st));
+        left = (int32_t)h[1 + level];
+        f.row_list = todo[level];
+        if (h[0] >= 0x7f800000u) break;      // values that are not finite: the plain engine
+    }
+    if (left > 0) {
+        f.rows = left;
+        f.buf = reinterpret_cast<Ent *>(buffers);
+        return run_f64(f, st);
+    }
+    return ANN_OK;
+}
+
+}  // namespace
 
 // Exact kNN of `rows` query rows against base; ids and distances written
 // to out_ids and out_f (float) and/or out_d (double).  Synchronises.
@@ -1011,12 +1235,9 @@ ann_status knn_run(const float *base, int64_t n, int dim, const float *queries, 
         a.out_f = out_f;
         a.out_d = out_d;
         a.cap = (int)knn_cap(K);
-        const int blocks = (int)((rows + knn::kRows - 1) / knn::kRows);
-        size_t lds = 4 * (size_t)a.cap * sizeof(Ent);
-        ANN_HIP(hipFuncSetAttribute((const void *)knn_f64_kernel,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-        hipLaunchKernelGGL(knn_f64_kernel, dim3(blocks), dim3(256), lds, st, a);
-        ANN_LAUNCHED();
+        // a workgroup's 256 rows stay below 2 GiB (buffer offsets)
+        ann_status s = dim <= (1 << 20) ? run_f16(a, flag, p, st) : run_f64(a, st);
+        if (s != ANN_OK) return s;
     }
     ANN_HIP(hipStreamSynchronize(st));
     return ANN_OK;

@@ -132,6 +132,74 @@ def test_gt_knn_duplicates_tie_by_id_and_exclude_self():
     assert (ids.cpu().numpy() == ref_ids).all()
 
 
+def _real_points(kind, n, nq, d):
+    # values on a dyadic grid, so that the FP64 distances are exact
+    r = np.random.default_rng(n + d)
+    x = np.rint(r.normal(size=(n + nq, d)) * 2 ** 10) / 2 ** 10
+    if kind == "copies":            # more equal rows than a list can hold
+        x[r.permutation(n)[:900]] = x[n]
+    elif kind == "tight":           # groups far narrower than their distance from the centre
+        x = x / 4 + r.integers(-900, 901, size=(12, d))[r.integers(0, 12, n + nq)]
+    elif kind == "large":
+        x = x * 2.0 ** 60
+    elif kind == "small":
+        x = x * 2.0 ** -60
+    elif kind == "flat":            # one wide dimension beside narrow ones
+        x[:, 0] *= 2 ** 8
+        x[:, 1:] = np.rint(x[:, 1:] * 2 ** 4) / 2 ** 10
+    elif kind == "outlier":
+        x[n // 2] = 2.0 ** 12
+    elif kind == "infinite":
+        x[n // 3, 0] = np.inf
+    x = x.astype(np.float32)
+    return x[:n], x[n:]
+
+
+@pytest.mark.parametrize("n,nq,d,k,kind", [
+    (3_000, 300, 100, 10, "normal"),       # ragged rows, columns and dimensions
+    (6_000, 1_025, 20, 64, "normal"),      # one row past a workgroup's 256 four times
+    (70_000, 3, 96, 100, "normal"),        # the rows' lists merged over column slices
+    (2_000, 300, 130, 1024, "normal"),     # largest k
+    (60, 3_000, 200, 100, "normal"),       # k above n: -1 padded
+    (4_000, 500, 64, 30, "copies"),
+    (5_000, 600, 48, 128, "tight"),
+    (3_000, 300, 68, 12, "large"),
+    (3_000, 300, 68, 12, "small"),
+    (3_000, 300, 68, 12, "flat"),
+    (3_000, 300, 68, 12, "outlier"),
+    (3_000, 300, 68, 12, "infinite"),
+])
+def test_real_valued_knn_matches_oracle(n, nq, d, k, kind):
+    base, q = _real_points(kind, n, nq, d)
+    say("case: real-valued kNN n=%d nq=%d d=%d k=%d %s" % (n, nq, d, k, kind))
+    ids, dist = _ann().ann_gt_knn(_dev(base), _dev(q), k)
+    torch.cuda.synchronize()
+    ids, dist = ids.cpu().numpy(), dist.cpu().numpy()
+    ref_ids, ref_d2 = oracle.knn(base, q, k)
+    assert (ids == ref_ids).all()
+    ok = ref_ids >= 0
+    assert (dist[ok] == ref_d2[ok].astype(np.float32)).all()
+    assert np.isinf(dist[~ok]).all()
+
+
+@pytest.mark.parametrize("n,d,k,kind", [(6_000, 100, 64, "normal"), (3_000, 36, 20, "copies"),
+                                        (9_001, 96, 128, "tight")])
+def test_real_valued_all_pairs_match_oracle(n, d, k, kind):
+    base, _ = _real_points(kind, n, 1, d)
+    say("case: real-valued all pairs n=%d d=%d k=%d %s" % (n, d, k, kind))
+    x = _dev(base)
+    ids, dist = _ann().ann_gt_knn(x, x, k, exclude_self=True)
+    torch.cuda.synchronize()
+    ids, dist = ids.cpu().numpy(), dist.cpu().numpy()
+    rows = np.arange(0, n, max(1, n // 400))
+    ref_ids, ref_d2 = oracle.knn(base, base[rows], k + 1)
+    for t, row in enumerate(rows):
+        # the row itself is first, except among copies of it, where ids order
+        keep = [j for j in range(k + 1) if ref_ids[t, j] != row][:k]
+        assert (ids[row] == ref_ids[t, keep]).all(), row
+        assert (dist[row] == ref_d2[t, keep].astype(np.float32)).all(), row
+
+
 def test_medoid_matches_oracle():
     ix = tiny_index()
     say("case: medoid")
