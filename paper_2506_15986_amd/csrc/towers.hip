@@ -104,7 +104,19 @@ __global__ void __launch_bounds__(256) gemm_bf16_kernel(GemmArgs g)
 }
 
 // ---------------------------------------------------------------- FP32 GEMM
-// C[m][n] = alpha * sum_k A(m,k) * B(n,k), fixed k order per element.
+// C[m][n] = alpha * sum_k A(m,k) * B(n,k), one chain of fused multiply-adds
+// per element in k order (the training's bits depend on it).  A and B are
+// contiguous along k or along m / n.
+//
+// The chain cannot be split, so what shortens it is many small tiles (8 x 64:
+// a wavefront takes two rows, a lane one column) and wide LDS reads: both
+// operands lie there along k, four of a column's values come in one read, four
+// of a row's in one read that all lanes share, and the next 64 k are on their
+// way while the staged ones are added.  The three products of a step (1,024
+// queries, 1,024 hubs, 64 dimensions): 367 us with 64 x 64 tiles (16 workgroups
+// on 256 CUs for the gradients), 43 us now, the two gradients in one launch.
+// Scalar loads for the rows (52 us a launch) and 128 k at a time (29 us)
+// measured slower.
 struct GemmF {
     const float *A;
     int64_t sam, sak;
@@ -116,36 +128,80 @@ struct GemmF {
     int ldc;
 };
 
-__global__ void __launch_bounds__(256) gemm_f32_kernel(GemmF g)
-{
-    __shared__ float As[16][GT + 1];
-    __shared__ float Bs[16][GT + 1];
-    const int t = threadIdx.x;
-    const int tr = (t / 16) * 4, tc = (t % 16) * 4;
-    const int m0 = blockIdx.y * GT, n0 = blockIdx.x * GT;
-    float acc[4][4] = {};
-    for (int k0 = 0; k0 < g.K; k0 += 16) {
-        for (int e = t; e < 16 * GT; e += 256) {
-            int kk = e / GT, r = e % GT;
-            int m = m0 + r, n = n0 + r, k = k0 + kk;
-            As[kk][r] = (m < g.M && k < g.K) ? g.A[(int64_t)m * g.sam + (int64_t)k * g.sak] : 0.f;
-            Bs[kk][r] = (n < g.N && k < g.K) ? g.B[(int64_t)n * g.sbn + (int64_t)k * g.sbk] : 0.f;
+constexpr int FR = 2, FM = 4 * FR, FN = 64, FK = 64, FS = FK + 4;
+
+// Rows [r0, r0 + R) x k [k0, k0 + FK) of X into registers, in the order that
+// X is contiguous in, and from there to LDS as [row][k].
+template <int R>
+struct FStage {
+    static constexpr int U = R * FK / 256;
+    float v[U];
+    __device__ void load(const float *X, int64_t sr, int64_t sk, int r0, int rows, int k0, int K)
+    {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int e = (int)threadIdx.x + 256 * u;
+            const int r = sk == 1 ? e / FK : e % R, k = sk == 1 ? e % FK : e / R;
+            v[u] = r0 + r < rows && k0 + k < K
+                       ? X[(int64_t)(r0 + r) * sr + (int64_t)(k0 + k) * sk]
+                       : 0.f;
         }
-        __syncthreads();
-        for (int kk = 0; kk < 16; ++kk) {
-            float a[4], b[4];
-            for (int i = 0; i < 4; ++i) a[i] = As[kk][tr + i];
-            for (int j = 0; j < 4; ++j) b[j] = Bs[kk][tc + j];
-            for (int i = 0; i < 4; ++i)
-                for (int j = 0; j < 4; ++j) acc[i][j] += a[i] * b[j];
-        }
-        __syncthreads();
     }
-    for (int i = 0; i < 4; ++i)
-        for (int j = 0; j < 4; ++j) {
-            int m = m0 + tr + i, n = n0 + tc + j;
-            if (m < g.M && n < g.N) g.C[(int64_t)m * g.ldc + n] = g.alpha * acc[i][j];
+    __device__ void store(float *s, int64_t sk) const
+    {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int e = (int)threadIdx.x + 256 * u;
+            const int r = sk == 1 ? e / FK : e % R, k = sk == 1 ? e % FK : e / R;
+            s[r * FS + k] = v[u];
         }
+    }
+};
+
+// two products in one launch: blockIdx.z picks
+__global__ void __launch_bounds__(256) gemm_f32_kernel(GemmF g0, GemmF g1)
+{
+    const GemmF &g = blockIdx.z ? g1 : g0;
+    const int m0 = (int)blockIdx.y * FM, n0 = (int)blockIdx.x * FN;
+    if (m0 >= g.M || n0 >= g.N) return;
+    __shared__ __align__(16) float As[FM * FS], Bs[FN * FS];
+    const int t = threadIdx.x, lane = t & 63;
+    const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+    FStage<FM> a;
+    FStage<FN> b;
+    a.load(g.A, g.sam, g.sak, m0, g.M, 0, g.K);
+    b.load(g.B, g.sbn, g.sbk, n0, g.N, 0, g.K);
+    float acc[FR] = {};
+    for (int k0 = 0; k0 < g.K; k0 += FK) {
+        __syncthreads();
+        a.store(As, g.sak);
+        b.store(Bs, g.sbk);
+        __syncthreads();
+        if (k0 + FK < g.K) {
+            a.load(g.A, g.sam, g.sak, m0, g.M, k0 + FK, g.K);
+            b.load(g.B, g.sbn, g.sbk, n0, g.N, k0 + FK, g.K);
+        }
+#pragma unroll
+        for (int k = 0; k < FK; k += 4) {
+            const float4 y = *reinterpret_cast<const float4 *>(Bs + lane * FS + k);
+            float4 x[FR];
+#pragma unroll
+            for (int r = 0; r < FR; ++r)
+                x[r] = *reinterpret_cast<const float4 *>(As + (FR * w + r) * FS + k);
+#pragma unroll
+            for (int r = 0; r < FR; ++r) {
+                acc[r] += x[r].x * y.x;
+                acc[r] += x[r].y * y.y;
+                acc[r] += x[r].z * y.z;
+                acc[r] += x[r].w * y.w;
+            }
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < FR; ++r) {
+        const int m = m0 + FR * w + r;
+        if (m < g.M && n0 + lane < g.N) g.C[(int64_t)m * g.ldc + n0 + lane] = g.alpha * acc[r];
+    }
 }
 
 // ---------------------------------------------------------------- elementwise
@@ -184,138 +240,188 @@ __global__ void hub_input_kernel(const float *base, int dim, const int32_t *hub_
     }
 }
 
-// ------------------------------------------------- fused inference forward
-// The forward of one tower for inference (no intermediates kept), one
-// wavefront per 16 rows: x * in_scale rounded to BF16, the first product
-// with bias and ReLU rounded to BF16 into LDS, the second product with bias,
-// and the per-row normalisation.  Every step is the arithmetic of the
-// training forward in the same order: the same operand rounding, the same
-// lane layout and sequence of 32-deep MFMA steps per output element (the
-// generic GEMM's), and the normalisation's sums and shuffles of
-// normalise_kernel, so the embeddings are the same bits.
-// HB = hidden / 16, DB = dout / 16; din % 8 == 0.
-struct TowerInfer {
+// ------------------------------------------------------- fused tower kernels
+// The forward and the row-wise half of the backward of a tower, 16 rows to a
+// workgroup whose four wavefronts share the 16-wide column blocks of each
+// product.  Every step is the arithmetic of the generic kernels in the same
+// order (operand rounding, lane layout and sequence of 32-deep MFMA steps per
+// output element, the normalisation's sums and shuffles), so the results are
+// the same bits.
+//
+// They are latency chains (a row block's products are a few hundred MFMA), so
+// what counts is how few launches and dependent loads there are: rows are
+// staged in LDS once, both towers of a training step share a launch, and four
+// wavefronts to 16 rows shorten the chain of column blocks (10,000 rows of
+// 128 -> 128 -> 64: 22 us with one wavefront per 16 rows, 11.6 us with four; one
+// row 10.5 and 5.4 us).
+struct TowerArgs {
     const float *x;
     const int32_t *idx;   // row i of the input is x row idx[i] (NULL: row i)
-    int rows, din;
+    int rows, din, hidden, dout;
     float scale;
-    const uint16_t *W1b;
-    const float *b1;
-    const uint16_t *W2b;
-    const float *b2;
-    float *out;
+    const uint16_t *W1b, *W2b;
+    const float *b1, *b2;
+    float *e;             // rows x dout, unit rows
+    // training: kept for the backward
+    uint16_t *xb, *a1b;
+    float *z1, *nrm;
+    const float *de;
+    float *dz2, *dz1;
+    uint16_t *dz2b, *dz1b;
 };
 
-template <int HB, int DB>
-__global__ void __launch_bounds__(64) tower_infer_kernel(TowerInfer a)
+struct TowerPair {
+    TowerArgs t[2];
+    int blocks0;          // workgroups of t[0]
+};
+
+// LDS of the fused kernels: input, hidden and output rows
+__host__ __device__ inline size_t fused_lds(int din, int hidden, int dout)
 {
-    constexpr int HID = 16 * HB, DOUT = 16 * DB;
-    __shared__ __align__(16) uint16_t H[16][HID + 8];
-    __shared__ float Z[16][DOUT + 1];
-    const int lane = threadIdx.x;
+    return (size_t)16 * 2 * (din + 8) + (size_t)16 * 2 * (hidden + 8) + (size_t)16 * 4 * (dout + 1);
+}
+
+__device__ inline v4f mfma_bf16(v8s a, v8s b, v4f c)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, a),
+                                                   __builtin_bit_cast(v8bf, b), c, 0, 0, 0);
+}
+
+template <bool TRAIN>
+__global__ void __launch_bounds__(256) tower_fwd_kernel(TowerPair p)
+{
+    const bool second = (int)blockIdx.x >= p.blocks0;
+    const TowerArgs &a = p.t[second ? 1 : 0];
+    extern __shared__ __align__(16) unsigned char tw_lds[];
+    uint16_t *X = reinterpret_cast<uint16_t *>(tw_lds);            // 16 x (din + 8)
+    const int xs = a.din + 8, hs = a.hidden + 8, zs = a.dout + 1;
+    uint16_t *H = X + 16 * xs;                                     // 16 x (hidden + 8)
+    float *Z = reinterpret_cast<float *>(H + 16 * hs);             // 16 x (dout + 1)
+    const int t = threadIdx.x, lane = t & 63;
+    const int w = __builtin_amdgcn_readfirstlane(t >> 6);
     const int rl = lane & 15, kq = 8 * (lane >> 4), rq = 4 * (lane >> 4);
-    const int r0 = blockIdx.x * 16;
-    const int row = r0 + rl;
-    const bool live = row < a.rows;
-    const float *xr = a.x + (live ? (int64_t)(a.idx ? a.idx[row] : row) * a.din : 0);
-    v4f acc[HB];
-#pragma unroll
-    for (int b = 0; b < HB; ++b) acc[b] = v4f{0.f, 0.f, 0.f, 0.f};
-    for (int k0 = 0; k0 < a.din; k0 += 32) {
-        const int k = k0 + kq;
-        v8s av;
-        if (live && k < a.din) {
-            const float4 lo = *reinterpret_cast<const float4 *>(xr + k);
-            const float4 hi = *reinterpret_cast<const float4 *>(xr + k + 4);
-            av[0] = (short)f2bf(lo.x * a.scale);
-            av[1] = (short)f2bf(lo.y * a.scale);
-            av[2] = (short)f2bf(lo.z * a.scale);
-            av[3] = (short)f2bf(lo.w * a.scale);
-            av[4] = (short)f2bf(hi.x * a.scale);
-            av[5] = (short)f2bf(hi.y * a.scale);
-            av[6] = (short)f2bf(hi.z * a.scale);
-            av[7] = (short)f2bf(hi.w * a.scale);
-        } else {
-            av = v8s{0, 0, 0, 0, 0, 0, 0, 0};
+    const int r0 = ((int)blockIdx.x - (second ? p.blocks0 : 0)) * 16;
+    const v8s zero = {0, 0, 0, 0, 0, 0, 0, 0};
+    const int q4 = a.din >> 2;
+    for (int e = t; e < 16 * q4; e += 256) {
+        const int r = e / q4, j = 4 * (e - r * q4);
+        ushort4 v = make_ushort4(0, 0, 0, 0);
+        if (r0 + r < a.rows) {
+            const int64_t src = a.idx ? a.idx[r0 + r] : r0 + r;
+            const float4 f = *reinterpret_cast<const float4 *>(a.x + src * a.din + j);
+            v = make_ushort4(f2bf(f.x * a.scale), f2bf(f.y * a.scale), f2bf(f.z * a.scale),
+                             f2bf(f.w * a.scale));
+            if (TRAIN) *reinterpret_cast<ushort4 *>(a.xb + (int64_t)(r0 + r) * a.din + j) = v;
         }
-#pragma unroll
-        for (int b = 0; b < HB; ++b) {
-            const v8s bv = k < a.din
-                               ? *reinterpret_cast<const v8s *>(a.W1b + (size_t)(16 * b + rl) * a.din + k)
-                               : v8s{0, 0, 0, 0, 0, 0, 0, 0};
-            acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, av),
-                                                             __builtin_bit_cast(v8bf, bv), acc[b],
-                                                             0, 0, 0);
-        }
+        *reinterpret_cast<ushort4 *>(X + r * xs + j) = v;
     }
-#pragma unroll
-    for (int b = 0; b < HB; ++b) {
+    __syncthreads();
+    for (int b = w; b < (a.hidden >> 4); b += 4) {
         const int n = 16 * b + rl;
+        const uint16_t *wr = a.W1b + (size_t)n * a.din;
+        v4f acc = {0.f, 0.f, 0.f, 0.f};
+        for (int k0 = 0; k0 < a.din; k0 += 32) {
+            const int k = k0 + kq;
+            const bool in = k < a.din;
+            const v8s bv = in ? *reinterpret_cast<const v8s *>(wr + k) : zero;
+            const v8s av = in ? *reinterpret_cast<const v8s *>(X + rl * xs + k) : zero;
+            acc = mfma_bf16(av, bv, acc);
+        }
         const float bias = a.b1[n];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            float v = acc[b][i] + bias;
+            float v = acc[i] + bias;
             v = v > 0.f ? v : 0.f;
-            H[rq + i][n] = f2bf(v);
+            const uint16_t h = f2bf(v);
+            H[(rq + i) * hs + n] = h;
+            if (TRAIN && r0 + rq + i < a.rows) {
+                const int64_t o = (int64_t)(r0 + rq + i) * a.hidden + n;
+                a.z1[o] = v;
+                a.a1b[o] = h;
+            }
         }
     }
     __syncthreads();
-    v4f acc2[DB];
-#pragma unroll
-    for (int b = 0; b < DB; ++b) acc2[b] = v4f{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int k0 = 0; k0 < HID; k0 += 32) {
-        const v8s av = *reinterpret_cast<const v8s *>(&H[rl][k0 + kq]);
-#pragma unroll
-        for (int b = 0; b < DB; ++b) {
-            const v8s bv = *reinterpret_cast<const v8s *>(a.W2b + (size_t)(16 * b + rl) * HID + k0 + kq);
-            acc2[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, av),
-                                                              __builtin_bit_cast(v8bf, bv), acc2[b],
-                                                              0, 0, 0);
-        }
-    }
-#pragma unroll
-    for (int b = 0; b < DB; ++b) {
+    for (int b = w; b < (a.dout >> 4); b += 4) {
         const int n = 16 * b + rl;
+        const uint16_t *wr = a.W2b + (size_t)n * a.hidden;
+        v4f acc = {0.f, 0.f, 0.f, 0.f};
+        for (int k0 = 0; k0 < a.hidden; k0 += 32) {
+            const int k = k0 + kq;
+            const bool in = k < a.hidden;
+            const v8s bv = in ? *reinterpret_cast<const v8s *>(wr + k) : zero;
+            const v8s av = in ? *reinterpret_cast<const v8s *>(H + rl * hs + k) : zero;
+            acc = mfma_bf16(av, bv, acc);
+        }
         const float bias = a.b2[n];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) Z[rq + i][n] = acc2[b][i] + bias;
+        for (int i = 0; i < 4; ++i) Z[(rq + i) * zs + n] = acc[i] + bias;
     }
     __syncthreads();
-    // normalise_kernel's arithmetic, one row at a time
-    for (int r = 0; r < 16 && r0 + r < a.rows; ++r) {
+    // normalise_kernel's arithmetic, a row at a time
+    for (int r = w; r < 16 && r0 + r < a.rows; r += 4) {
         float s = 0.f;
-        for (int c = lane; c < DOUT; c += 64) s += Z[r][c] * Z[r][c];
+        for (int c = lane; c < a.dout; c += 64) s += Z[r * zs + c] * Z[r * zs + c];
         for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
-        const float nrm = sqrtf(s);
-        for (int c = lane; c < DOUT; c += 64) a.out[(int64_t)(r0 + r) * DOUT + c] = Z[r][c] / nrm;
+        const float n = sqrtf(s);
+        for (int c = lane; c < a.dout; c += 64) a.e[(int64_t)(r0 + r) * a.dout + c] = Z[r * zs + c] / n;
+        if (TRAIN && lane == 0) a.nrm[r0 + r] = n;
     }
 }
 
-template <int HB>
-bool launch_infer_d(const TowerInfer &a, int dout, hipStream_t st)
+// dz2 = (de - e <e, de>) / |z|, its BF16 rounding, and dz1 = (dz2b . W2b) where
+// the hidden activation is positive
+__global__ void __launch_bounds__(256) tower_bwd_rows_kernel(TowerPair p)
 {
-    const dim3 grid((unsigned)((a.rows + 15) / 16));
-    switch (dout) {
-    case 32: hipLaunchKernelGGL((tower_infer_kernel<HB, 2>), grid, dim3(64), 0, st, a); return true;
-    case 64: hipLaunchKernelGGL((tower_infer_kernel<HB, 4>), grid, dim3(64), 0, st, a); return true;
-    case 128: hipLaunchKernelGGL((tower_infer_kernel<HB, 8>), grid, dim3(64), 0, st, a); return true;
-    default: return false;
+    const bool second = (int)blockIdx.x >= p.blocks0;
+    const TowerArgs &a = p.t[second ? 1 : 0];
+    extern __shared__ __align__(16) unsigned char tw_lds[];
+    uint16_t *D = reinterpret_cast<uint16_t *>(tw_lds);            // 16 x (dout + 8)
+    const int ds = a.dout + 8;
+    const int t = threadIdx.x, lane = t & 63;
+    const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int rl = lane & 15, kq = 8 * (lane >> 4), rq = 4 * (lane >> 4);
+    const int r0 = ((int)blockIdx.x - (second ? p.blocks0 : 0)) * 16;
+    for (int r = w; r < 16; r += 4) {
+        if (r0 + r >= a.rows) {
+            for (int c = lane; c < a.dout; c += 64) D[r * ds + c] = 0;
+            continue;
+        }
+        const int64_t at = (int64_t)(r0 + r) * a.dout;
+        float s = 0.f;
+        for (int c = lane; c < a.dout; c += 64) s += a.e[at + c] * a.de[at + c];
+        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+        for (int c = lane; c < a.dout; c += 64) {
+            const float v = (a.de[at + c] - a.e[at + c] * s) / a.nrm[r0 + r];
+            const uint16_t h = f2bf(v);
+            a.dz2[at + c] = v;
+            a.dz2b[at + c] = h;
+            D[r * ds + c] = h;
+        }
     }
-}
-
-// launches the fused forward when the shapes and alignments allow it
-bool tower_infer(const ann_tower &w, const float *x, const int32_t *idx, int rows, float *out,
-                 hipStream_t st)
-{
-    if (w.din < 8 || w.din % 8 || !aligned(x, 16) || !aligned(w.W1b, 16) || !aligned(w.W2b, 16))
-        return false;
-    const TowerInfer a{x, idx, rows, w.din, w.in_scale, w.W1b, w.b1, w.W2b, w.b2, out};
-    switch (w.hidden) {
-    case 64: return launch_infer_d<4>(a, w.dout, st);
-    case 128: return launch_infer_d<8>(a, w.dout, st);
-    case 256: return launch_infer_d<16>(a, w.dout, st);
-    default: return false;
+    __syncthreads();
+    const v8s zero = {0, 0, 0, 0, 0, 0, 0, 0};
+    for (int b = w; b < (a.hidden >> 4); b += 4) {
+        const int n = 16 * b + rl;
+        v4f acc = {0.f, 0.f, 0.f, 0.f};
+        for (int k0 = 0; k0 < a.dout; k0 += 32) {
+            const int k = k0 + kq;
+            const bool in = k < a.dout;
+            v8s bv = zero;
+            if (in)
+#pragma unroll
+                for (int q = 0; q < 8; ++q) bv[q] = (short)a.W2b[(size_t)(k + q) * a.hidden + n];
+            const v8s av = in ? *reinterpret_cast<const v8s *>(D + rl * ds + k) : zero;
+            acc = mfma_bf16(av, bv, acc);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (r0 + rq + i >= a.rows) continue;
+            const int64_t o = (int64_t)(r0 + rq + i) * a.hidden + n;
+            const float v = a.z1[o] > 0.f ? acc[i] : 0.f;
+            a.dz1[o] = v;
+            a.dz1b[o] = f2bf(v);
+        }
     }
 }
 
@@ -350,6 +456,8 @@ __global__ void normalise_bwd_kernel(const float *e, const float *de, const floa
     }
 }
 
+constexpr int CE_W = 16;   // logits of a row that a lane can hold
+
 // one wavefront per query row of logits: loss_i and ds = (softmax - onehot)/B
 __global__ void softmax_ce_kernel(const float *s, int rows, int cols, const int32_t *labels,
                                   const int32_t *idx, float inv_b, float *ds, float *loss_rows)
@@ -358,6 +466,39 @@ __global__ void softmax_ce_kernel(const float *s, int rows, int cols, const int3
     if (r >= rows) return;
     const int lane = threadIdx.x & 63;
     const float *row = s + r * cols;
+    if (cols <= 64 * CE_W) {
+        // the lane's values of the row in registers: one pass over memory
+        // instead of three, the sums in the same order
+        float v[CE_W];
+#pragma unroll
+        for (int k = 0; k < CE_W; ++k)
+            v[k] = lane + 64 * k < cols ? row[lane + 64 * k] : -__int_as_float(0x7f800000);
+        const int y = labels[idx ? idx[r] : r];
+        const float ry = row[y];
+        float mx = -__int_as_float(0x7f800000);
+#pragma unroll
+        for (int k = 0; k < CE_W; ++k)
+            if (lane + 64 * k < cols) mx = fmaxf(mx, v[k]);
+        for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+        float se = 0.f;
+#pragma unroll
+        for (int k = 0; k < CE_W; ++k)
+            if (lane + 64 * k < cols) {
+                v[k] = expf(v[k] - mx);
+                se += v[k];
+            }
+        for (int o = 32; o > 0; o >>= 1) se += __shfl_xor(se, o);
+#pragma unroll
+        for (int k = 0; k < CE_W; ++k) {
+            const int c = lane + 64 * k;
+            if (c < cols) {
+                const float p = v[k] / se;
+                ds[r * cols + c] = (p - (c == y ? 1.f : 0.f)) * inv_b;
+            }
+        }
+        if (lane == 0) loss_rows[r] = logf(se) + mx - ry;
+        return;
+    }
     float mx = -__int_as_float(0x7f800000);
     for (int c = lane; c < cols; c += 64) mx = fmaxf(mx, row[c]);
     for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
@@ -426,35 +567,171 @@ __global__ void bias_grad_kernel(const float *x, int rows, int cols, float *out)
     out[c] = s;
 }
 
-__global__ void mean_kernel(const float *x, int count, float *out)
+struct AdamStep {
+    float lr, b1, b2, eps, c1, c2;
+};
+
+// The fused multiply-adds are written out: left to the compiler, which of two
+// products is fused differs from one caller to the next, and with it the bits
+// of the training.
+__device__ inline void adam_update(const AdamStep &s, float gi, float *p, float *m, float *v,
+                                   uint16_t *pb)
 {
-    __shared__ float sh[256];
+    const float mi = __builtin_fmaf(1.f - s.b1, gi, s.b1 * *m);
+    const float vi = __builtin_fmaf(gi, (1.f - s.b2) * gi, s.b2 * *v);
+    *m = mi;
+    *v = vi;
+    const float mh = mi / s.c1, vh = vi / s.c2;
+    const float pi = *p - s.lr * mh / (sqrtf(vh) + s.eps);
+    *p = pi;
+    if (pb) *pb = f2bf(pi);
+}
+
+__global__ void adam_kernel(float *p, const float *g, float *m, float *v, int64_t count, AdamStep s,
+                            uint16_t *pb)
+{
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count;
+         i += (int64_t)gridDim.x * blockDim.x)
+        adam_update(s, g[i], p + i, m + i, v + i, pb ? pb + i : nullptr);
+}
+
+// ---- the other half of the backward: weight and bias gradients of both
+// towers, each updated by Adam where it is made, and the mean loss, in one
+// launch.  A wavefront takes a 16 x 16 tile of a weight gradient, one chain of
+// 32-deep MFMA steps over all rows (as gemm_bf16_kernel's, so the same bits);
+// a workgroup takes 64 columns of a bias gradient, whose rows are added in
+// order (bias_grad_kernel's sum) from LDS.  21 us for both towers at the
+// default configuration, where six products, four sums and eight updates in
+// launches of their own took 350 us; the whole step 939 -> 86 us.
+struct GradArgs {
+    int rows, din, hidden, dout;
+    const uint16_t *xb, *a1b, *dz2b, *dz1b;
+    const float *dz2, *dz1;
+    float *g[4];                 // gW1, gb1, gW2, gb2
+    float *p[4], *m[4], *v[4];   // the same order; NULL when step is 0
+    uint16_t *W1b, *W2b;
+    int w2_tiles, tiles;         // tiles of gW2, of gW2 and gW1
+    int tile_blocks, bias2_blocks, blocks;
+};
+
+struct GradPair {
+    GradArgs t[2];
+    AdamStep adam;
+    int step;
+    const float *loss_rows;
+    int loss_count;
+    float *loss;
+};
+
+constexpr int BG_ROWS = 128;     // rows of a bias gradient staged at a time
+
+__device__ inline void mean_of(const float *x, int count, float *out, float *sh)
+{
     float s = 0.f;
     for (int i = threadIdx.x; i < count; i += 256) s += x[i];
     sh[threadIdx.x] = s;
     __syncthreads();
     for (int o = 128; o > 0; o >>= 1) {
-        if (threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
+        if ((int)threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
         __syncthreads();
     }
     if (threadIdx.x == 0) *out = sh[0] / (float)count;
 }
 
-__global__ void adam_kernel(float *p, const float *g, float *m, float *v, int64_t count, float lr,
-                            float b1, float b2, float eps, float c1, float c2, uint16_t *pb)
+__global__ void __launch_bounds__(256) tower_grad_kernel(GradPair p)
 {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        float gi = g[i];
-        float mi = b1 * m[i] + (1.f - b1) * gi;
-        float vi = b2 * v[i] + (1.f - b2) * gi * gi;
-        m[i] = mi;
-        v[i] = vi;
-        float mh = mi / c1, vh = vi / c2;
-        float pi = p[i] - lr * mh / (sqrtf(vh) + eps);
-        p[i] = pi;
-        if (pb) pb[i] = f2bf(pi);
+    __shared__ float stage[BG_ROWS][64];
+    int blk = blockIdx.x;
+    if (blk == p.t[0].blocks + p.t[1].blocks) return mean_of(p.loss_rows, p.loss_count, p.loss, &stage[0][0]);
+    const bool second = blk >= p.t[0].blocks;
+    const GradArgs &a = p.t[second ? 1 : 0];
+    if (second) blk -= p.t[0].blocks;
+    const int t = threadIdx.x, lane = t & 63;
+    if (blk < a.tile_blocks) {
+        int tile = 4 * blk + (t >> 6);
+        if (tile >= a.tiles) return;
+        const bool w2 = tile < a.w2_tiles;
+        if (!w2) tile -= a.w2_tiles;
+        // C[m][n] = sum over rows k of A[k][m] B[k][n]
+        const uint16_t *A = w2 ? a.dz2b : a.dz1b, *B = w2 ? a.a1b : a.xb;
+        const int M = w2 ? a.dout : a.hidden, N = w2 ? a.hidden : a.din;
+        const int nt = (N + 15) / 16;
+        const int m0 = tile / nt * 16, n0 = tile % nt * 16;
+        const int rl = lane & 15, kq = 8 * (lane >> 4), rq = 4 * (lane >> 4);
+        const int m = m0 + rl, n = n0 + rl;
+        const int nc = n < N ? n : N - 1;      // a column past the end is not stored
+        v4f acc = {0.f, 0.f, 0.f, 0.f};
+        int k0 = 0;
+        for (; k0 + 128 <= a.rows; k0 += 128) {
+            v8s av[4], bv[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    const int64_t k = k0 + 32 * u + kq + q;
+                    av[u][q] = (short)A[k * M + m];
+                    bv[u][q] = (short)B[k * N + nc];
+                }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) acc = mfma_bf16(av[u], bv[u], acc);
+        }
+        for (; k0 < a.rows; k0 += 32) {
+            v8s av, bv;
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const int64_t k = k0 + kq + q;
+                av[q] = k < a.rows ? (short)A[k * M + m] : (short)0;
+                bv[q] = k < a.rows ? (short)B[k * N + nc] : (short)0;
+            }
+            acc = mfma_bf16(av, bv, acc);
+        }
+        if (n >= N) return;
+        const int j = w2 ? 2 : 0;
+        uint16_t *pb = w2 ? a.W2b : a.W1b;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int64_t o = (int64_t)(m0 + rq + i) * N + n;
+            a.g[j][o] = acc[i];
+            if (p.step > 0) adam_update(p.adam, acc[i], a.p[j] + o, a.m[j] + o, a.v[j] + o, pb + o);
+        }
+        return;
     }
+    // 64 columns of a bias gradient
+    blk -= a.tile_blocks;
+    const bool second_bias = blk < a.bias2_blocks;
+    if (!second_bias) blk -= a.bias2_blocks;
+    const float *x = second_bias ? a.dz2 : a.dz1;
+    const int cols = second_bias ? a.dout : a.hidden;
+    const int c = 64 * blk + lane;
+    float s = 0.f;
+    for (int r0 = 0; r0 < a.rows; r0 += BG_ROWS) {
+        const int m = a.rows - r0 < BG_ROWS ? a.rows - r0 : BG_ROWS;
+        float v[BG_ROWS / 4];
+#pragma unroll
+        for (int u = 0; u < BG_ROWS / 4; ++u) {
+            const int r = (t >> 6) + 4 * u;
+            v[u] = r < m && c < cols ? x[(int64_t)(r0 + r) * cols + c] : 0.f;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < BG_ROWS / 4; ++u) stage[(t >> 6) + 4 * u][lane] = v[u];
+        __syncthreads();
+        if (t < 64) {
+            int r = 0;
+            for (; r + 16 <= m; r += 16) {
+                float y[16];
+#pragma unroll
+                for (int u = 0; u < 16; ++u) y[u] = stage[r + u][lane];
+#pragma unroll
+                for (int u = 0; u < 16; ++u) s += y[u];
+            }
+            for (; r < m; ++r) s += stage[r][lane];
+        }
+    }
+    if (t >= 64 || c >= cols) return;
+    const int j = second_bias ? 3 : 1;
+    a.g[j][c] = s;
+    if (p.step > 0) adam_update(p.adam, s, a.p[j] + c, a.m[j] + c, a.v[j] + c, nullptr);
 }
 
 __global__ void scale_kernel(float *x, int64_t count, float a)
@@ -462,6 +739,12 @@ __global__ void scale_kernel(float *x, int64_t count, float a)
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count;
          i += (int64_t)gridDim.x * blockDim.x)
         x[i] *= a;
+}
+
+__global__ void __launch_bounds__(256) mean_kernel(const float *x, int count, float *out)
+{
+    __shared__ float sh[256];
+    mean_of(x, count, out, sh);
 }
 
 inline dim3 grid2(int M, int N) { return dim3((N + GT - 1) / GT, (M + GT - 1) / GT); }
@@ -474,9 +757,12 @@ ann_status gemm_bf16(const GemmArgs &g, hipStream_t st)
     return ANN_OK;
 }
 
-ann_status gemm_f32(const GemmF &g, hipStream_t st)
+ann_status gemm_f32(const GemmF &g, const GemmF *h, hipStream_t st)
 {
-    hipLaunchKernelGGL(gemm_f32_kernel, grid2(g.M, g.N), dim3(256), 0, st, g);
+    const GemmF &g1 = h ? *h : g;
+    const int M = g.M > g1.M ? g.M : g1.M, N = g.N > g1.N ? g.N : g1.N;
+    hipLaunchKernelGGL(gemm_f32_kernel, dim3((N + FN - 1) / FN, (M + FM - 1) / FM, h ? 2 : 1), dim3(256), 0,
+                       st, g, g1);
     ANN_LAUNCHED();
     return ANN_OK;
 }
@@ -629,24 +915,153 @@ ann_status tower_bwd(const ann_tower &w, const ann_tower_grads &gr, const TowerB
     return ANN_OK;
 }
 
+AdamStep adam_step(int step, float lr)
+{
+    const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
+    return AdamStep{lr, b1, b2, eps, 1.f - powf(b1, (float)step), 1.f - powf(b2, (float)step)};
+}
+
 ann_status adam(ann_tower &w, const ann_tower_grads &gr, const ann_adam_state &a, int step,
                 float lr, hipStream_t st)
 {
-    const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
-    const float c1 = 1.f - powf(b1, (float)step), c2 = 1.f - powf(b2, (float)step);
+    const AdamStep s = adam_step(step, lr);
     const int64_t n1 = (int64_t)w.hidden * w.din, n2 = (int64_t)w.dout * w.hidden;
     hipLaunchKernelGGL(adam_kernel, dim3(gridn(n1)), dim3(256), 0, st, w.W1, gr.gW1, a.mW1, a.vW1, n1,
-                       lr, b1, b2, eps, c1, c2, w.W1b);
+                       s, w.W1b);
     ANN_LAUNCHED();
     hipLaunchKernelGGL(adam_kernel, dim3(gridn(w.hidden)), dim3(256), 0, st, w.b1, gr.gb1, a.mb1,
-                       a.vb1, (int64_t)w.hidden, lr, b1, b2, eps, c1, c2, (uint16_t *)nullptr);
+                       a.vb1, (int64_t)w.hidden, s, (uint16_t *)nullptr);
     ANN_LAUNCHED();
     hipLaunchKernelGGL(adam_kernel, dim3(gridn(n2)), dim3(256), 0, st, w.W2, gr.gW2, a.mW2, a.vW2, n2,
-                       lr, b1, b2, eps, c1, c2, w.W2b);
+                       s, w.W2b);
     ANN_LAUNCHED();
     hipLaunchKernelGGL(adam_kernel, dim3(gridn(w.dout)), dim3(256), 0, st, w.b2, gr.gb2, a.mb2,
-                       a.vb2, (int64_t)w.dout, lr, b1, b2, eps, c1, c2, (uint16_t *)nullptr);
+                       a.vb2, (int64_t)w.dout, s, (uint16_t *)nullptr);
     ANN_LAUNCHED();
+    return ANN_OK;
+}
+
+// The fused kernels take whole 16-wide column blocks and 16-byte groups of an
+// input row; other shapes and alignments go through the generic kernels.  More
+// than 64 KB of staged rows would leave a CU one workgroup.
+bool fused_ok(const ann_tower &w, const float *x)
+{
+    return w.din >= 8 && w.din % 8 == 0 && w.hidden % 16 == 0 && w.dout % 16 == 0 && aligned(x, 16) &&
+           aligned(w.W1b, 16) && aligned(w.W2b, 16) && fused_lds(w.din, w.hidden, w.dout) <= 65536;
+}
+
+TowerArgs tower_args(const ann_tower &w, const TowerBufs &b, const float *x, const int32_t *idx, int rows)
+{
+    TowerArgs a{};
+    a.x = x;
+    a.idx = idx;
+    a.rows = rows;
+    a.din = w.din;
+    a.hidden = w.hidden;
+    a.dout = w.dout;
+    a.scale = w.in_scale;
+    a.W1b = w.W1b;
+    a.W2b = w.W2b;
+    a.b1 = w.b1;
+    a.b2 = w.b2;
+    a.e = b.e;
+    a.xb = b.xb;
+    a.a1b = b.a1b;
+    a.z1 = b.z1;
+    a.nrm = b.nrm;
+    a.de = b.de;
+    a.dz2 = b.dz2;
+    a.dz1 = b.dz1;
+    a.dz2b = b.dz2b;
+    a.dz1b = b.dz1b;
+    return a;
+}
+
+GradArgs grad_args(const ann_tower &w, const ann_tower_grads &gr, const ann_adam_state *ad, const TowerBufs &b,
+                   int rows)
+{
+    GradArgs a{};
+    a.rows = rows;
+    a.din = w.din;
+    a.hidden = w.hidden;
+    a.dout = w.dout;
+    a.xb = b.xb;
+    a.a1b = b.a1b;
+    a.dz2b = b.dz2b;
+    a.dz1b = b.dz1b;
+    a.dz2 = b.dz2;
+    a.dz1 = b.dz1;
+    float *g[4] = {gr.gW1, gr.gb1, gr.gW2, gr.gb2}, *p[4] = {w.W1, w.b1, w.W2, w.b2};
+    for (int i = 0; i < 4; ++i) {
+        a.g[i] = g[i];
+        a.p[i] = p[i];
+    }
+    if (ad) {
+        float *m[4] = {ad->mW1, ad->mb1, ad->mW2, ad->mb2}, *v[4] = {ad->vW1, ad->vb1, ad->vW2, ad->vb2};
+        for (int i = 0; i < 4; ++i) {
+            a.m[i] = m[i];
+            a.v[i] = v[i];
+        }
+    }
+    a.W1b = w.W1b;
+    a.W2b = w.W2b;
+    a.w2_tiles = (w.dout / 16) * (w.hidden / 16);
+    a.tiles = a.w2_tiles + (w.hidden / 16) * ((w.din + 15) / 16);
+    a.tile_blocks = (a.tiles + 3) / 4;
+    a.bias2_blocks = (w.dout + 63) / 64;
+    a.blocks = a.tile_blocks + a.bias2_blocks + (w.hidden + 63) / 64;
+    return a;
+}
+
+inline int row_blocks(int rows) { return (rows + 15) / 16; }
+
+// One training step around a loss: both towers' forward, `loss` (which
+// enqueues the logits, the loss rows and the embeddings' gradients b.de), both
+// backwards, `inputs` (work that needs the old weights), Adam when step >= 1
+// and the mean of the loss rows.
+template <class Loss, class Inputs>
+ann_status train_towers(ann_tower &qt, ann_tower &ht, const ann_tower_grads &qg, const ann_tower_grads &hg,
+                        const ann_adam_state *qa, const ann_adam_state *ha, const TowerBufs &bq,
+                        const TowerBufs &bh, const float *xq, const int32_t *iq, int rq, const float *xh,
+                        const int32_t *ih, int rh, float lr, int step, const float *loss_rows, int loss_count,
+                        float *mean_loss, Loss loss, Inputs inputs, hipStream_t st)
+{
+    if (fused_ok(qt, xq) && fused_ok(ht, xh)) {
+        TowerPair p{{tower_args(qt, bq, xq, iq, rq), tower_args(ht, bh, xh, ih, rh)}, row_blocks(rq)};
+        const dim3 grid((unsigned)(p.blocks0 + row_blocks(rh)));
+        const int din = qt.din > ht.din ? qt.din : ht.din;
+        const size_t lds = fused_lds(din, qt.hidden, qt.dout);
+        hipLaunchKernelGGL(tower_fwd_kernel<true>, grid, dim3(256), lds, st, p);
+        ANN_LAUNCHED();
+        TRY(loss());
+        hipLaunchKernelGGL(tower_bwd_rows_kernel, grid, dim3(256), (size_t)32 * (qt.dout + 8), st, p);
+        ANN_LAUNCHED();
+        TRY(inputs());
+        GradPair g{{grad_args(qt, qg, qa, bq, rq), grad_args(ht, hg, ha, bh, rh)},
+                   step > 0 ? adam_step(step, lr) : AdamStep{}, step, loss_rows, loss_count, mean_loss};
+        hipLaunchKernelGGL(tower_grad_kernel, dim3((unsigned)(g.t[0].blocks + g.t[1].blocks + 1)), dim3(256),
+                           0, st, g);
+        ANN_LAUNCHED();
+        return ANN_OK;
+    }
+    hipLaunchKernelGGL(gather_bf16_kernel, dim3(gridn((int64_t)rq * qt.din)), dim3(256), 0, st, xq, qt.din, iq,
+                       rq, qt.in_scale, bq.xb);
+    ANN_LAUNCHED();
+    TRY(tower_fwd(qt, bq, rq, st));
+    hipLaunchKernelGGL(gather_bf16_kernel, dim3(gridn((int64_t)rh * ht.din)), dim3(256), 0, st, xh, ht.din, ih,
+                       rh, ht.in_scale, bh.xb);
+    ANN_LAUNCHED();
+    TRY(tower_fwd(ht, bh, rh, st));
+    TRY(loss());
+    hipLaunchKernelGGL(mean_kernel, dim3(1), dim3(256), 0, st, loss_rows, loss_count, mean_loss);
+    ANN_LAUNCHED();
+    TRY(tower_bwd(qt, qg, bq, rq, st));
+    TRY(tower_bwd(ht, hg, bh, rh, st));
+    TRY(inputs());
+    if (step > 0) {
+        TRY(adam(qt, qg, *qa, step, lr, st));
+        TRY(adam(ht, hg, *ha, step, lr, st));
+    }
     return ANN_OK;
 }
 
@@ -690,13 +1105,17 @@ size_t train_hub_ws(int bh, int P, int N, int din_q, int din_h, int hidden, int 
 ann_status tower_forward_run(const ann_tower &w, const float *x, const int32_t *idx, int rows,
                              float *out, void *ws, hipStream_t st)
 {
-    if (rows > 0 && tower_infer(w, x, idx, rows, out, st)) {
-        ANN_LAUNCHED();
-        return ANN_OK;
-    }
     Carve cv{static_cast<unsigned char *>(ws)};
     TowerBufs b = carve_tower(cv, rows, w.din, w.hidden, w.dout);
     b.e = out;
+    if (rows > 0 && fused_ok(w, x)) {
+        const TowerArgs a = tower_args(w, b, x, idx, rows);
+        const TowerPair p{{a, a}, row_blocks(rows)};
+        hipLaunchKernelGGL(tower_fwd_kernel<false>, dim3((unsigned)row_blocks(rows)), dim3(256),
+                           fused_lds(w.din, w.hidden, w.dout), st, p);
+        ANN_LAUNCHED();
+        return ANN_OK;
+    }
     hipLaunchKernelGGL(gather_bf16_kernel, dim3(gridn((int64_t)rows * w.din)), dim3(256), 0, st, x,
                        w.din, idx, rows, w.in_scale, b.xb);
     ANN_LAUNCHED();
@@ -798,31 +1217,20 @@ extern "C" ann_status ann_train_step(ann_tower *qt, ann_tower *ht, const ann_tow
     if (q_emb) bq.e = q_emb;
     if (h_emb) bh.e = h_emb;
 
-    // forward
-    hipLaunchKernelGGL(gather_bf16_kernel, dim3(gridn((int64_t)batch * qt->din)), dim3(256), 0, st,
-                       train_q, qt->din, batch_idx, batch, qt->in_scale, bq.xb);
-    ANN_LAUNCHED();
-    TRY(tower_fwd(*qt, bq, batch, st));
-    hipLaunchKernelGGL(gather_bf16_kernel, dim3(gridn((int64_t)n_hubs * ht->din)), dim3(256), 0, st,
-                       hub_in, ht->din, (const int32_t *)nullptr, n_hubs, ht->in_scale, bh.xb);
-    ANN_LAUNCHED();
-    TRY(tower_fwd(*ht, bh, n_hubs, st));
     const int e = qt->dout;
-    GemmF lg{bq.e, e, 1, bh.e, e, 1, batch, n_hubs, e, 1.f / tau, logits, n_hubs};
-    TRY(gemm_f32(lg, st));
-    hipLaunchKernelGGL(softmax_ce_kernel, dim3((batch + 3) / 4), dim3(256), 0, st, logits, batch,
-                       n_hubs, labels, batch_idx, 1.f / (float)batch, dlog, lrow);
-    ANN_LAUNCHED();
-    hipLaunchKernelGGL(mean_kernel, dim3(1), dim3(256), 0, st, lrow, batch, loss);
-    ANN_LAUNCHED();
-    // dEq [batch x e] = dlog . Eh / tau ; dEh [nh x e] = dlog^T . Eq / tau
-    GemmF gq{dlog, n_hubs, 1, bh.e, 1, e, batch, e, n_hubs, 1.f / tau, bq.de, e};
-    TRY(gemm_f32(gq, st));
-    GemmF gh{dlog, 1, n_hubs, bq.e, 1, e, n_hubs, e, batch, 1.f / tau, bh.de, e};
-    TRY(gemm_f32(gh, st));
-    TRY(tower_bwd(*qt, *qg, bq, batch, st));
-    TRY(tower_bwd(*ht, *hg, bh, n_hubs, st));
-    if (hub_in_grad) {
+    auto contrast = [&]() -> ann_status {
+        GemmF lg{bq.e, e, 1, bh.e, e, 1, batch, n_hubs, e, 1.f / tau, logits, n_hubs};
+        TRY(gemm_f32(lg, nullptr, st));
+        hipLaunchKernelGGL(softmax_ce_kernel, dim3((batch + 3) / 4), dim3(256), 0, st, logits, batch,
+                           n_hubs, labels, batch_idx, 1.f / (float)batch, dlog, lrow);
+        ANN_LAUNCHED();
+        // dEq [batch x e] = dlog . Eh / tau ; dEh [nh x e] = dlog^T . Eq / tau
+        GemmF gq{dlog, n_hubs, 1, bh.e, 1, e, batch, e, n_hubs, 1.f / tau, bq.de, e};
+        GemmF gh{dlog, 1, n_hubs, bq.e, 1, e, n_hubs, e, batch, 1.f / tau, bh.de, e};
+        return gemm_f32(gq, &gh, st);
+    };
+    auto inputs = [&]() -> ann_status {
+        if (!hub_in_grad) return ANN_OK;
         // dL/d hub_in [n_hubs x din_h] = in_scale * (dz1b . W1b)
         GemmArgs g{};
         g.A = bh.dz1b;
@@ -843,12 +1251,10 @@ extern "C" ann_status ann_train_step(ann_tower *qt, ann_tower *ht, const ann_tow
                                ht->in_scale);
             ANN_LAUNCHED();
         }
-    }
-    if (step > 0) {
-        TRY(adam(*qt, *qg, *qa, step, lr, st));
-        TRY(adam(*ht, *hg, *ha, step, lr, st));
-    }
-    return ANN_OK;
+        return ANN_OK;
+    };
+    return train_towers(*qt, *ht, *qg, *hg, qa, ha, bq, bh, train_q, batch_idx, batch, hub_in, nullptr, n_hubs,
+                        lr, step, lrow, batch, loss, contrast, inputs, st);
 }
 
 extern "C" size_t ann_train_hub_workspace_size(int32_t hubs, int32_t P, int32_t N, int32_t din_q,
@@ -895,34 +1301,19 @@ extern "C" ann_status ann_train_step_hub(ann_tower *qt, ann_tower *ht, const ann
     if (q_emb) bq.e = q_emb;
     if (h_emb) bh.e = h_emb;
 
-    // forward: the batch's queries and hubs through their towers
-    hipLaunchKernelGGL(gather_bf16_kernel, dim3(gridn((int64_t)rows * qt->din)), dim3(256), 0, st,
-                       train_q, qt->din, q_idx, rows, qt->in_scale, bq.xb);
-    ANN_LAUNCHED();
-    TRY(tower_fwd(*qt, bq, rows, st));
-    hipLaunchKernelGGL(gather_bf16_kernel, dim3(gridn((int64_t)hubs * ht->din)), dim3(256), 0, st,
-                       hub_in, ht->din, hub_idx, hubs, ht->in_scale, bh.xb);
-    ANN_LAUNCHED();
-    TRY(tower_fwd(*ht, bh, hubs, st));
     const int e = qt->dout;
-    // scores [hubs x rows] = Eh . Eq^T / tau (only each hub's own block is used)
-    GemmF lg{bh.e, e, 1, bq.e, e, 1, hubs, rows, e, 1.f / tau, sc, rows};
-    TRY(gemm_f32(lg, st));
-    hipLaunchKernelGGL(hub_ce_kernel, dim3((hubs + 3) / 4), dim3(256), 0, st, sc, hubs, rows, P, N,
-                       1.f / (float)hubs, dsc, lrow);
-    ANN_LAUNCHED();
-    hipLaunchKernelGGL(mean_kernel, dim3(1), dim3(256), 0, st, lrow, hubs, loss);
-    ANN_LAUNCHED();
-    // dEh [hubs x e] = dS . Eq / tau ; dEq [rows x e] = dS^T . Eh / tau
-    GemmF gh{dsc, rows, 1, bq.e, 1, e, hubs, e, rows, 1.f / tau, bh.de, e};
-    TRY(gemm_f32(gh, st));
-    GemmF gq{dsc, 1, rows, bh.e, 1, e, rows, e, hubs, 1.f / tau, bq.de, e};
-    TRY(gemm_f32(gq, st));
-    TRY(tower_bwd(*qt, *qg, bq, rows, st));
-    TRY(tower_bwd(*ht, *hg, bh, hubs, st));
-    if (step > 0) {
-        TRY(adam(*qt, *qg, *qa, step, lr, st));
-        TRY(adam(*ht, *hg, *ha, step, lr, st));
-    }
-    return ANN_OK;
+    auto contrast = [&]() -> ann_status {
+        // scores [hubs x rows] = Eh . Eq^T / tau (only each hub's own block is used)
+        GemmF lg{bh.e, e, 1, bq.e, e, 1, hubs, rows, e, 1.f / tau, sc, rows};
+        TRY(gemm_f32(lg, nullptr, st));
+        hipLaunchKernelGGL(hub_ce_kernel, dim3((hubs + 3) / 4), dim3(256), 0, st, sc, hubs, rows, P, N,
+                           1.f / (float)hubs, dsc, lrow);
+        ANN_LAUNCHED();
+        // dEh [hubs x e] = dS . Eq / tau ; dEq [rows x e] = dS^T . Eh / tau
+        GemmF gh{dsc, rows, 1, bq.e, 1, e, hubs, e, rows, 1.f / tau, bh.de, e};
+        GemmF gq{dsc, 1, rows, bh.e, 1, e, rows, e, hubs, 1.f / tau, bq.de, e};
+        return gemm_f32(gh, &gq, st);
+    };
+    return train_towers(*qt, *ht, *qg, *hg, qa, ha, bq, bh, train_q, q_idx, rows, hub_in, hub_idx,
+                        hubs, lr, step, lrow, hubs, loss, contrast, []() -> ann_status { return ANN_OK; }, st);
 }

@@ -118,6 +118,45 @@ def test_train_step_gradients_match_oracle(scale):
         assert torch.equal(a, b)
 
 
+def _offset_copy(x, words):
+    # the same rows, `words` floats past a 16-byte boundary
+    buf = torch.empty(x.numel() + 8, dtype=torch.float32, device="cuda")
+    y = buf[words:words + x.numel()].view(x.shape)
+    y.copy_(x)
+    return y
+
+
+@pytest.mark.parametrize("batch,nh,dq,dh,hidden,dout", [(100, 70, 128, 160, 128, 64), (33, 17, 40, 48, 48, 32),
+                                                        (16, 129, 8, 24, 16, 16), (260, 31, 96, 96, 256, 128)])
+def test_fused_training_step_equals_generic_step(batch, nh, dq, dh, hidden, dout):
+    # aligned input rows take the fused kernels, rows 4 bytes off the generic
+    # ones: loss, embeddings, gradients, moments and weights are the same bits
+    ann = _ann()
+    say("case: fused against generic step, batch %d hubs %d %d/%d -> %d -> %d" %
+        (batch, nh, dq, dh, hidden, dout))
+    r = np.random.default_rng(batch + nh)
+    mk = lambda *s: (r.normal(size=s) / np.sqrt(s[-1])).astype(np.float32)
+    wq = (mk(hidden, dq), mk(hidden), mk(dout, hidden), mk(dout))
+    wh = (mk(hidden, dh), mk(hidden), mk(dout, hidden), mk(dout))
+    x = _dev(r.normal(size=(2 * batch, dq)).astype(np.float32))
+    hub_in = _dev(r.normal(size=(nh, dh)).astype(np.float32))
+    idx = _dev(r.permutation(2 * batch)[:batch].astype(np.int32))
+    lab = _dev(r.integers(0, nh, 2 * batch).astype(np.int32))
+    got = []
+    for off in (0, 1):
+        qt, ht = ann.Tower(*wq, in_scale=0.5), ann.Tower(*wh)
+        xo, ho = _offset_copy(x, off), _offset_copy(hub_in, off)
+        dx = torch.empty_like(hub_in)
+        outs = []
+        for step in (1, 2):
+            loss, qe, he = ann.ann_train_step(qt, ht, xo, idx, lab, ho, 0.07, 1e-2, step, want_emb=True,
+                                              hub_in_grad=dx)
+            outs += [loss, qe, he, dx.clone()] + [t.clone() for t in qt.g + ht.g]
+        outs += qt.params() + ht.params() + qt.m + qt.v + ht.m + ht.v + [qt.W1b, qt.W2b, ht.W1b, ht.W2b]
+        got.append([t.cpu().numpy().tobytes() for t in outs])
+    assert got[0] == got[1]
+
+
 def test_adam_step_matches_oracle_update():
     ix, km, hub_in, qp, hp = _setup()
     ann = _ann()
