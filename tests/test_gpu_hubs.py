@@ -117,6 +117,38 @@ def test_hub_features_match_oracle():
     assert np.allclose(f.cpu().numpy(), ref, rtol=0, atol=1e-4)
 
 
+@pytest.mark.parametrize("n,dim,R,h,wcap", [
+    (900, 6, 64, 3, 1),       # the hub alone; rows that are no float4 rows
+    (900, 6, 64, 4, 17),      # the cap falls inside the first batch of nodes
+    (3000, 20, 64, 5, 1000),  # the cap falls inside a full batch, 64-wide rows
+    (3000, 20, 7, 250, 4096), # no cap: the walk ends by itself, odd row length
+    (5000, 33, 48, 5, 4096),  # the largest cap crossed
+])
+def test_hub_features_walk_edges(n, dim, R, h, wcap):
+    # whole numbers of the walk exactly, features as closely as FP64 sums in
+    # another order allow once rounded to FP32 (2^-24 relative, and 1e-6 of
+    # the unit-scale features)
+    rng = np.random.default_rng(n + R)
+    base = (np.rint(rng.normal(0, 40, size=(n, dim)))).astype(np.float32)
+    g = rng.integers(0, n, size=(n, R)).astype(np.int32)
+    for v in range(n):   # distinct neighbours, no self edge, rows of any length
+        row = np.unique(g[v][g[v] != v])[:rng.integers(0, R + 1)]
+        g[v] = -1
+        g[v, :row.size] = rng.permutation(row)
+    nh = 40
+    hubs = rng.choice(n, nh, replace=False).astype(np.int32)
+    asg = rng.integers(0, nh, size=n).astype(np.int32)
+    cen = rng.normal(0, 30, size=(nh, dim))
+    say("case: hub features walk n=%d R=%d h=%d wcap=%d" % (n, R, h, wcap))
+    ref, ref_ws = oracle.hub_features(base, g, 5, hubs, asg, cen, h=h, wcap=wcap,
+                                      standardize=False)
+    f, ws = _ann().ann_hub_features(_dev(base), _dev(g), 5, _dev(hubs), _dev(asg), _dev(cen),
+                                    h=h, wcap=wcap, standardise=False)
+    torch.cuda.synchronize()
+    assert (ws.cpu().numpy() == ref_ws).all()
+    assert np.allclose(f.cpu().numpy(), ref, rtol=1e-5, atol=1e-6)
+
+
 @pytest.mark.parametrize("which,k,levels,lam,iters", [
     ("int", 8, 2, 1.0, 5),       # integers 0..255, 64 clusters
     ("tiny", 4, 3, 0.5, 4),      # grid data, 64 clusters over 3 rounds
