@@ -470,6 +470,16 @@ struct Searcher {
     // expanded, so the expansion order does not depend on the prediction.
     __device__ SearchResult run(uint32_t entry, int Lq, int32_t *trace, int trace_cap)
     {
+        return run_until(entry, Lq, trace, trace_cap, [](int, const SearchResult &, bool) { return false; });
+    }
+
+    // The same, asked before each expansion whether to end there: stop(place
+    // of the next entry to expand, state so far, whether this lane's filter
+    // has lost an id), the same answer in every lane.
+    template <typename Stop>
+    __device__ __forceinline__ SearchResult run_until(uint32_t entry, int Lq, int32_t *trace,
+                                                      int trace_cap, Stop stop)
+    {
         const int lane = beam::lane_id();
         SearchResult r{0, 0, 0, false};
         vis.clear();
@@ -494,7 +504,7 @@ struct Searcher {
         for (;;) {
             int ppos, npos;
             next_two_unexpanded(cursor, ppos, npos);
-            if (ppos < 0) break;
+            if (ppos < 0 || stop(ppos, r, lost)) break;
             cursor = ppos;
             const uint32_t p = ids(cur)[ppos] & beam::kIdMask;
             int nb = -1;
@@ -618,6 +628,12 @@ struct Searcher {
         }
         r.lost = __ballot(lost) != 0;
         return r;
+    }
+
+    // id at place t of the pool, -1 past its end
+    __device__ int32_t id_at(int t) const
+    {
+        return t < cnt ? (int32_t)(ids(cur)[t] & beam::kIdMask) : -1;
     }
 
     __device__ void write_topk(int kq, int k_max, int32_t *oid, float *odist)

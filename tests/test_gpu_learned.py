@@ -682,6 +682,52 @@ def test_labels_overflowing_the_visited_table_are_searched_again():
     assert (lab == ref_lab).all()
 
 
+@pytest.mark.parametrize("case", ["tables", "chunks"])
+def test_labels_row_lists(case):
+    ann = _ann()
+    if case == "tables":
+        # points on a line, 64 edges forward: a search visits every point
+        # between its hub and the query, so with a ladder to 40 (2^11 slots at
+        # first) the hubs' searches fit, need 2^13 slots or need 2^14; distances are whole numbers whose order FP32 keeps
+        n, R, M = 9100, 64, 4
+        base = np.zeros((n, 4), np.float32)
+        base[:, 0] = np.arange(n)
+        g = np.arange(n)[:, None] + 1 + np.arange(R)[None, :]
+        g = np.where(g < n, g, -1).astype(np.int32)
+        q = np.zeros((70, 4), np.float32)
+        q[:, 0] = 8980 + np.arange(70)
+        truth, _ = oracle.knn(base, q, 10)
+        hubs = np.array([8700, 7300, 4400, 3], np.int32)
+        cand = np.tile(np.arange(M, dtype=np.int32), (70, 1))
+        say("case: labels by row lists, tables")
+        ref_lab, ref_tab = oracle.make_labels(base, g, q, truth, cand, hubs, [10, 12, 40], 10)
+        lab, tab, flags = ann.ann_make_labels(_dev(base), _dev(g), _dev(q), _dev(truth), 10,
+                                              _dev(cand), _dev(hubs), [10, 12, 40])
+        torch.cuda.synchronize()
+        assert (flags.cpu().numpy() == 0).all()
+        assert (tab.cpu().numpy() == ref_tab).all()
+        assert (lab.cpu().numpy() == ref_lab).all()
+        return
+    # more rows than are searched together (2^20): the same labels as the
+    # same queries in two calls
+    ix = int_index()
+    base, g = _dev(ix["base"]), _dev(ix["graph"])
+    r = np.random.default_rng(5)
+    M, nq = 4000, 301
+    q = _dev(r.integers(0, 256, size=(nq, ix["base"].shape[1])).astype(np.float32))
+    hubs = _dev(r.integers(0, ix["base"].shape[0], size=M).astype(np.int32))
+    cand = torch.arange(M, dtype=torch.int32, device="cuda").repeat(nq, 1).contiguous()
+    truth = ann.ann_gt_knn(base, q, 10)[0]
+    say("case: labels by row lists, chunks")
+    one = ann.ann_make_labels(base, g, q, truth, 9, cand, hubs, [10, 16])
+    parts = [ann.ann_make_labels(base, g, q[a:b].contiguous(), truth[a:b].contiguous(), 9,
+                                 cand[a:b].contiguous(), hubs, [10, 16])
+             for a, b in ((0, 100), (100, nq))]
+    torch.cuda.synchronize()
+    for i in range(3):
+        assert torch.equal(one[i], torch.cat([p[i] for p in parts]))
+
+
 def test_trained_entry_beats_untrained_towers_and_medoid():
     # What the trained network gains over the method without it (the paper's
     # ablation without the learned part): the same index, hubs, features and
