@@ -20,9 +20,11 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
          "-I", os.path.join(HERE, "..", "include")]
 
 
-# per-file options: the int8 kNN engine's matrix-core accumulators in VGPRs,
-# so its distance tests read them without AGPR-to-VGPR moves
-FILE_FLAGS = {"knn.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+# per-file options: the kNN engines' and the k-means assignment's matrix-core
+# accumulators in VGPRs, so their distance tests read them without
+# AGPR-to-VGPR moves
+_VGPR_FORM = ["-mllvm", "-amdgpu-mfma-vgpr-form"]
+FILE_FLAGS = {"knn.hip": _VGPR_FORM, "kmeans.hip": _VGPR_FORM}
 
 
 def _compile(src, verbose):

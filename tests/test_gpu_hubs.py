@@ -83,6 +83,44 @@ def test_select_hubs_bit_exact_special_shapes(case):
     assert (hub.cpu().numpy() == ref["hub_ids"]).all()
 
 
+@pytest.mark.parametrize("case,n,dim,nh,iters", [
+    ("ints", 5000, 20, 33, 6),        # one fragment of 32 dimensions, part of it
+    ("ints", 5000, 64, 100, 6),       # two
+    ("offset", 4000, 96, 70, 6),      # three, far from the origin
+    ("ints", 3001, 200, 64, 5),       # eight
+    ("ints", 2000, 400, 40, 4),       # sixteen
+    ("ints", 1500, 1000, 24, 4),      # thirty-two
+    ("ints", 900, 128, 1, 3),         # a single centroid
+    ("outlier", 4000, 128, 65, 5),    # a point beyond FP16's range
+    ("tight", 40000, 32, 64, 3),      # sixteen near centroids in each far place:
+                                      # more points left than the class search takes
+    ("tight", 3000, 32, 64, 3),       # ... and fewer
+    ("ints", 17000, 4, 16400, 2),     # more centroids than the FP16 products take
+])
+def test_select_hubs_bit_exact_assignment_paths(case, n, dim, nh, iters):
+    r = np.random.default_rng(n + dim)
+    if case == "ints":
+        base = r.integers(0, 256, size=(n, dim)).astype(np.float32)
+    elif case == "offset":
+        base = (3000 + np.rint(r.normal(0, 40, size=(n, dim)) * 256) / 256).astype(np.float32)
+    elif case == "outlier":
+        base = r.integers(0, 256, size=(n, dim)).astype(np.float32)
+        base[17] = 2.0 ** 27
+    else:
+        place = 2000.0 * r.integers(-1, 2, size=(4, dim))
+        base = (place[r.integers(0, 4, size=n)] +
+                np.rint(r.normal(0, 1, size=(n, dim)) * 256) / 256).astype(np.float32)
+    init = r.choice(n, nh, replace=False).astype(np.int32)
+    say("case: select_hubs %s n=%d dim=%d nh=%d" % (case, n, dim, nh))
+    ref = oracle.kmeans_hubs(base, nh, iters, init)
+    hub, cen, asg, steps = _ann().ann_select_hubs(_dev(base), nh, iters, _dev(init))
+    torch.cuda.synchronize()
+    assert steps == ref["steps"]
+    assert (asg.cpu().numpy() == ref["assign"]).all()
+    assert (cen.cpu().numpy() == ref["centroids"]).all()
+    assert (hub.cpu().numpy() == ref["hub_ids"]).all()
+
+
 def test_select_hubs_empty_cluster():
     x = np.zeros((8, 4), np.float32)
     x[:, 0] = [0, 0, 10, 11, 0, 0, 10, 11]
