@@ -228,16 +228,22 @@ __global__ void __launch_bounds__(256) knn_f64_kernel(KnnArgs a)
 // (l % 16) of A (resp. column (l % 16) of B) at k offset 8 * (l / 16); the
 // result element i of lane l is C[4 * (l / 16) + i][l % 16].
 //
-// Selection.  A slice is visited in increasing column order, so a column can
-// enter a row's best Kp only if its d2 is strictly below the Kp-th best d2
-// seen so far (an equal d2 loses the tie to the smaller id already held).
-// With t = |x'|^2 - thr per row, the test d2 < thr is 2 x'.y' - |y'|^2 > t:
-// one shift-add and one compare per distance, and a wave ballot skips the
-// append path when no lane passes.  Passing columns are appended to the
-// row's buffer (global memory, cap entries of (d2 << 32 | column)); before a
-// tile could overflow it, the owning wave sorts the buffer in LDS, keeps the
-// best Kp and tightens thr.  A second kernel merges the slices of each row,
-// drops the row's own column when asked, and writes the K best.
+// Selection.  A column can be among a row's best Kp only if its d2 does not
+// exceed the Kp-th best d2 seen so far (thr).  With the products started at
+// half the column's negated norm the test is one subtraction and a share of a
+// maximum per distance, against bounds held in registers, and a wave ballot
+// skips the append path when no lane passes.  Passing columns are appended to
+// the row's buffer (global memory, cap entries of (d2 << 32 | column)); before
+// a tile could overflow it, the owning wave cuts the buffer to about the best
+// Kp by a bisection on d2 and tightens thr; the slice's end sorts it.  A second
+// kernel merges the slices of each row, drops the row's own column when
+// asked, and writes the K best.
+//
+// Bound by the tiles' arrival (a column tile is requested one tile ahead) and
+// the tests beside the products: 1,000,000 x 128 with itself, K = 64, 152 ms
+// (1,690 TOP/s; 198 with the bounds in LDS, a compare per distance and sorts
+// for cuts); 300,000 x 128, K = 128, 24 ms (43; the products and tests alone
+// 15).
 namespace i8 {
 
 constexpr int kRowsWG = 256;
@@ -317,6 +323,50 @@ __device__ inline int sort_keep(uint64_t *g, int c, int Kp, uint64_t *s, int32_t
     return keep;
 }
 
+// One wave: drop entries of g that cannot be among the best Kp.  Finds by
+// bisection a d2 bound T that at least Kp and if possible at most Kp + slack of
+// the c entries (all <= top) meet, and keeps those, in no particular order;
+// returns their count and sets thr to T.  c >= Kp, c <= 64 E.  A sort of 256
+// entries by exchanges in LDS took 36 passes where this takes about ten counts
+// of registers.
+template <int E>
+__device__ inline int cut_keep(uint64_t *g, int c, int Kp, int slack, int32_t top, int32_t &thr)
+{
+    const int lane = __lane_id();
+    uint64_t v[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int t = 64 * e + lane;
+        v[e] = t < c ? g[t] : ~0ull;
+    }
+    // T + 2^(bit + 1) - 1 is a bound that at least Kp entries meet
+    uint32_t T = 0;
+    for (int bit = 31 - __builtin_clz((unsigned)top | 1u); bit >= 0; --bit) {
+        const uint32_t mid = T + (1u << bit) - 1u;
+        int m = 0;
+#pragma unroll
+        for (int e = 0; e < E; ++e) m += __popcll(__builtin_amdgcn_ballot_w64((uint32_t)(v[e] >> 32) <= mid));
+        if (m < Kp) {
+            T += 1u << bit;
+        } else if (m <= Kp + slack) {
+            T = mid;
+            break;
+        }
+    }
+    int keep = 0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const bool in = (uint32_t)(v[e] >> 32) <= T;
+        const uint64_t b = __builtin_amdgcn_ballot_w64(in);
+        const int at = keep + (int)__builtin_amdgcn_mbcnt_hi(
+                                  (uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u));
+        if (in) g[at] = v[e];
+        keep += __popcll(b);
+    }
+    thr = (int32_t)T;
+    return keep;
+}
+
 template <int KS>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KS <= 4 ? 3 : 2))) tiles_kernel(Args a)
 {
@@ -328,8 +378,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KS <= 
     int32_t *Bn = reinterpret_cast<int32_t *>(dyn + (2 * kCols * STRIDE + 15) / 16 * 16);
     int32_t *Bid = Bn + 2 * kCols;          // the columns' reported ids
     int32_t *r_an = Bid + 2 * kCols;
-    // per row: |q'|^2 - thr - 1, the bound the distance test compares with
-    // (in LDS, read per column block, to leave registers to the operands)
+    // per row: |q'|^2 - thr - 1, the bound that 2 x'.y' - |y'|^2 must exceed
     int32_t *r_tv = r_an + kRowsWG;
     int32_t *r_cnt = r_tv + kRowsWG;
     const int t = threadIdx.x;
@@ -450,33 +499,62 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KS <= 
         ring_n = 0;
     };
 
+    // The rows' bounds for the first test, halved (see there), of this lane's
+    // rows of the 16 x 16 blocks: read from LDS for every column block they took
+    // more of the LDS's time than the operands.
+    int32_t tv[4][4];
+    auto load_bounds = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int rb = 0; rb < 4; ++rb) {
+            const int4 v = *reinterpret_cast<const int4 *>(r_tv + 64 * w + 16 * rb + 4 * (lane >> 4));
+            tv[rb][0] = (v.x - 1) >> 1;
+            tv[rb][1] = (v.y - 1) >> 1;
+            tv[rb][2] = (v.z - 1) >> 1;
+            tv[rb][3] = (v.w - 1) >> 1;
+        }
+    };
+
+    // operands and norm of a column block
+    long long bnext[KS];
+    int32_t nnext = 0;
+    auto read_block = [&](int cur, int cb) __attribute__((always_inline)) {
+        const int cl = 16 * cb + (lane & 15);
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+            bnext[ks] = *reinterpret_cast<const long long *>(
+                Bs + (size_t)(cur * kCols + cl) * STRIDE + 32 * ks + 8 * (lane >> 4));
+        nnext = Bn[cur * kCols + cl];
+    };
+
     Stage sg;
     if (ntiles > 0) {
         fetch(0, sg);
         store(0, 0, sg);
     }
     __syncthreads();
+    load_bounds();
     for (int it = 0; it < ntiles; ++it) {
         const int cur = it & 1;
+        read_block(cur, 0);
         // unrolled: a loop here makes the compiler wait for the tile loads in
         // flight before entering it
 #pragma unroll
         for (int cb = 0; cb < 4; ++cb) {
-            const int cl = 16 * cb + (lane & 15);
             long long bf[KS];
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks)
-                bf[ks] = *reinterpret_cast<const long long *>(
-                    Bs + (size_t)(cur * kCols + cl) * STRIDE + 32 * ks + 8 * (lane >> 4));
-            // the column's norm, negated in LDS so that 2 * dot - |x'|^2 is one
-            // shift-and-add
-            const int32_t nbc = Bn[cur * kCols + cl];
+            for (int ks = 0; ks < KS; ++ks) bf[ks] = bnext[ks];
+            // the column's norm, negated in LDS; the products start at half of it
+            const int32_t nbc = nnext;
+            // the next block's operands, so that its products find them there
+            if (cb < 3) read_block(cur, cb + 1);
+            const int32_t half = nbc >> 1;
+            const v4i first = {half, half, half, half};
             // the four row blocks' products first (independent accumulators,
             // so the matrix core pipelines them), then the tests
             v4i acc[4];
 #pragma unroll
             for (int rb = 0; rb < 4; ++rb) {
-                acc[rb] = v4i{0, 0, 0, 0};
+                acc[rb] = first;
                 // pairs of 32-byte k-steps on the 64-deep CDNA4 instruction:
                 // each lane's 16 bytes are its two 8-byte chunks, the same
                 // (row or column, k) correspondence for both operands, so the
@@ -498,39 +576,49 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KS <= 
                     acc[rb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(av, bv, acc[rb], 0, 0, 0);
                 }
             }
-            // 2 * dot - |x'|^2 > |q'|^2 - thr - 1  <=>  d2 <= thr: one shift-add
-            // and one compare per distance, one ballot for the 16 of this
-            // lane.  An equal d2 is let in (the sort orders ties by id), so
-            // the columns may come in any order.
-            bool p[4][4];
-            bool any = false;
+            // d2 <= thr  <=>  2 dot + nbc > r_tv.  With nbc = 2 half + odd and
+            // acc = dot + half that is 2 acc + odd > r_tv, which implies
+            // acc > floor((r_tv - 1) / 2): one compare per distance, one ballot
+            // for the 16 of this lane, and the odd bit is looked at for those
+            // that pass.  An equal d2 is let in (the sort orders ties by id),
+            // so the columns may come in any order.
+            // (The largest difference, not sixteen compares: those put their
+            // results where the scalar unit waits for each.)
+            int32_t most = -0x7fffffff;
 #pragma unroll
             for (int rb = 0; rb < 4; ++rb) {
-                const int4 tv = *reinterpret_cast<const int4 *>(r_tv + 64 * w + 16 * rb +
-                                                                4 * (lane >> 4));
-                p[rb][0] = (acc[rb][0] << 1) + nbc > tv.x;
-                p[rb][1] = (acc[rb][1] << 1) + nbc > tv.y;
-                p[rb][2] = (acc[rb][2] << 1) + nbc > tv.z;
-                p[rb][3] = (acc[rb][3] << 1) + nbc > tv.w;
-                any |= p[rb][0] | p[rb][1] | p[rb][2] | p[rb][3];
+                const int32_t a0 = acc[rb][0] - tv[rb][0], a1 = acc[rb][1] - tv[rb][1];
+                const int32_t a2 = acc[rb][2] - tv[rb][2], a3 = acc[rb][3] - tv[rb][3];
+                const int32_t m0 = a0 > a1 ? a0 : a1, m1 = a2 > a3 ? a2 : a3;
+                most = most > m0 ? most : m0;
+                most = most > m1 ? most : m1;
             }
-            if (__builtin_amdgcn_ballot_w64(any)) {
+            if (__builtin_amdgcn_ballot_w64(most > 0)) {
                 // a candidate takes its row's next buffer slot now and waits
                 // in the wave's LDS ring; the ring goes out to the buffers in
                 // one pass later (global stores here would keep the next
-                // products waiting for them)
+                // products waiting for them).  The lane is opaque here: row
+                // addresses made before the loop would be kept in scratch, and
+                // a reload waits for the next tile's loads.
+                int sl = lane;
+                asm volatile("" : "+v"(sl));
+                const int rq = 64 * w + 4 * (sl >> 4);
 #pragma unroll
                 for (int rb = 0; rb < 4; ++rb)
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        const uint64_t m = __builtin_amdgcn_ballot_w64(p[rb][i]);
+                        const bool near = acc[rb][i] > tv[rb][i];
+                        if (!__builtin_amdgcn_ballot_w64(near)) continue;
+                        const int rl = rq + 16 * rb + i;
+                        const int32_t v = 2 * acc[rb][i] + (nbc & 1);
+                        const bool in = near && v > r_tv[rl];
+                        const uint64_t m = __builtin_amdgcn_ballot_w64(in);
                         if (!m) continue;
-                        if (p[rb][i]) {
-                            const int rl = 64 * w + 16 * rb + 4 * (lane >> 4) + i;
-                            const int32_t d2 = r_an[rl] - nbc - 2 * acc[rb][i];
+                        if (in) {
+                            const int32_t d2 = r_an[rl] - v;
                             const int slot = atomicAdd(&r_cnt[rl], 1);
                             const uint64_t word = ((uint64_t)(uint32_t)d2 << 32) |
-                                                  (uint32_t)Bid[cur * kCols + cl];
+                                                  (uint32_t)Bid[cur * kCols + 16 * cb + (sl & 15)];
                             const int pos = ring_n + (int)__builtin_amdgcn_mbcnt_hi(
                                 (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
                             if (pos < kRing) {
@@ -563,14 +651,27 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KS <= 
                 full &= full - 1;
                 int32_t thr;
                 uint64_t *g = a.buf + ((row0 + r) * a.slices + slice) * (int64_t)a.cap;
-                const int keep = sort_keep(g, r_cnt[r], a.Kp, scratch, thr);
+                const int c = r_cnt[r];
+                const int32_t top = r_an[r] - r_tv[r] - 1;
+                const int slack = (a.cap - kCols - a.Kp) / 8;
+                int keep = a.cap;
+                if (a.cap <= 128) keep = cut_keep<2>(g, c, a.Kp, slack, top, thr);
+                else if (a.cap <= 256) keep = cut_keep<4>(g, c, a.Kp, slack, top, thr);
+                else if (a.cap <= 512) keep = cut_keep<8>(g, c, a.Kp, slack, top, thr);
+                // large lists, and lists that equal distances keep too long
+                if (keep > a.cap - kCols) {
+                    __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+                    knn::wsync();
+                    keep = sort_keep(g, a.cap <= 512 ? keep : c, a.Kp, scratch, thr);
+                }
                 if (lane == 0) {
                     r_cnt[r] = keep;
                     r_tv[r] = r_an[r] - thr - 1;
                 }
                 knn::wsync();
             }
-            __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);     // the sorts' stores, as above
+            __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);     // the stores, as above
+            load_bounds();
         }
         if (it + 1 < ntiles) store(it + 1, cur ^ 1, sg);
         __syncthreads();

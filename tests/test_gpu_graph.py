@@ -78,6 +78,22 @@ def test_int8_engine_slices_and_ties(n, nq, d, k, vmax):
     assert np.isinf(dist.cpu().numpy()[~ok]).all()
 
 
+@pytest.mark.parametrize("k", [64, 65, 192, 193, 448, 449])
+@pytest.mark.parametrize("d,vmax", [(32, 0), (64, 1), (96, 255)])
+def test_int8_engine_list_cuts(k, d, vmax):
+    # the edges of the lists' sizes (128, 256, 512 and larger), with all
+    # distances equal, with many equal ones and with hardly any
+    r = np.random.default_rng(k + d)
+    base = r.integers(0, vmax + 1, size=(4001, d)).astype(np.float32)
+    q = r.integers(0, vmax + 1, size=(70, d)).astype(np.float32)
+    say("case: int8 kNN list cuts k=%d d=%d values 0..%d" % (k, d, vmax))
+    ids, dist = _ann().ann_gt_knn(_dev(base), _dev(q), k)
+    torch.cuda.synchronize()
+    ref_ids, ref_d2 = oracle.knn(base, q, k)
+    assert (ids.cpu().numpy() == ref_ids).all()
+    assert (dist.cpu().numpy() == ref_d2.astype(np.float32)).all()
+
+
 def test_int8_engine_exclude_self_with_duplicates():
     # rows repeated several times: the row's own column is dropped, its
     # duplicates stay (distance 0, by id)
