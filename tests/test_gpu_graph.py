@@ -291,6 +291,29 @@ def test_build_graph_repair_bit_exact(which):
     assert (g.cpu().numpy() == ref).all()
 
 
+@pytest.mark.parametrize("n,d,K,R,alpha,kind", [
+    (700, 6, 9, 5, 1.2, "grid"),        # rows that are no float4s; a list that is no whole group
+    (700, 20, 30, 32, 1.0, "small"),    # many exact ties a2 d2 == dpc; as few candidates as R allows
+    (900, 128, 33, 32, 1.1, "grid"),    # the row a lane holds in registers, all of it
+    (600, 300, 40, 64, 1.2, "grid"),    # more than it holds
+    (600, 36, 24, 16, 1.2, "huge"),     # squares beyond FP32
+    (600, 36, 24, 16, 1.2, "tiny"),     # ... and below it
+])
+def test_build_graph_prune_bit_exact(n, d, K, R, alpha, kind):
+    r = np.random.default_rng(n + d)
+    if kind == "small":
+        base = r.integers(0, 3, size=(n, d)).astype(np.float32)
+    else:
+        base = (np.rint(r.normal(0, 1, size=(n, d)) * 256) / 256).astype(np.float32)
+        base *= np.float32({"huge": 2.0 ** 70, "tiny": 2.0 ** -80}.get(kind, 1.0))
+    say("case: prune n=%d d=%d K=%d R=%d %s" % (n, d, K, R, kind))
+    ref, med, nf, nr, _, _ = oracle.build_graph(base, K, R, alpha)
+    g, gm, (gf, gr) = _ann().ann_build_graph(_dev(base), K, R, alpha)
+    torch.cuda.synchronize()
+    assert gm == med and (gf, gr) == (nf, nr)
+    assert (g.cpu().numpy() == ref).all()
+
+
 def test_build_graph_partitioned_bit_exact():
     # candidates among the members of each point's home group (k-means
     # clusters, a second group for a third of the points, repeats, a home
