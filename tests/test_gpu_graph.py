@@ -295,7 +295,7 @@ def test_build_graph_repair_bit_exact(which):
     (700, 6, 9, 5, 1.2, "grid"),        # rows that are no float4s; a list that is no whole group
     (700, 20, 30, 32, 1.0, "small"),    # many exact ties a2 d2 == dpc; as few candidates as R allows
     (900, 128, 33, 32, 1.1, "grid"),    # the row a lane holds in registers, all of it
-    (600, 300, 40, 64, 1.2, "grid"),    # more than it holds
+    (600, 300, 70, 64, 1.2, "grid"),    # more than it holds
     (600, 36, 24, 16, 1.2, "huge"),     # squares beyond FP32
     (600, 36, 24, 16, 1.2, "tiny"),     # ... and below it
 ])
