@@ -298,19 +298,35 @@ struct Visited {
         const unsigned long long tag = h & ((1u << tag_bits) - 1u);
         const unsigned long long rep = tag * kOnes;
         unsigned long long *w = reinterpret_cast<unsigned long long *>(t) + set;
-#pragma unroll 1
-        for (int it = 0; it < 8; ++it) {
-            const unsigned long long old = __atomic_load_n(w, __ATOMIC_RELAXED);
+        // the first try in line: a second one is needed only when two lanes
+        // meet in a set, and a loop's exits cost more than the try
+        unsigned long long old = __atomic_load_n(w, __ATOMIC_RELAXED);
+        bool open = true, fresh = false;
+        auto attempt = [&]() __attribute__((always_inline)) {
             const unsigned long long x = old ^ rep;
-            if ((x - kOnes) & ~x & kTops) return false;
+            if ((x - kOnes) & ~x & kTops) {
+                open = false;
+                return;
+            }
             const unsigned long long nw = ((old << 12) | tag) & kWays;
-            if (atomicCAS(w, old, nw) == old) {
+            const unsigned long long was = atomicCAS(w, old, nw);
+            if (was == old) {
                 if (((old >> 48) & 0xFFFu) != 0xFFFu) lost = true;
-                return true;
+                open = false;
+                fresh = true;
+            }
+            old = was;
+        };
+        attempt();
+        if (__ballot(open)) {
+#pragma unroll 1
+            for (int it = 1; it < 8 && open; ++it) attempt();
+            if (open) {
+                lost = true;
+                fresh = true;
             }
         }
-        lost = true;
-        return true;
+        return fresh;
     }
 };
 

@@ -130,8 +130,11 @@ struct Searcher {
         beam::wave_sync();
     }
 
-    __device__ inline K *keys(int c) const { return c ? pk1 : pk0; }
-    __device__ inline uint32_t *ids(int c) const { return c ? pi1 : pi0; }
+    __device__ inline K *keys(int c) const { return __builtin_amdgcn_readfirstlane(c) ? pk1 : pk0; }
+    __device__ inline uint32_t *ids(int c) const
+    {
+        return __builtin_amdgcn_readfirstlane(c) ? pi1 : pi0;
+    }
 
     __device__ static inline D partial(const float4 &x, const float4 &y)
     {
@@ -144,7 +147,11 @@ struct Searcher {
     template <int W = 1>
     __device__ void distances(int m, int w = 0)
     {
-        if (chunks == G * CPL)
+        // opaque: a mask of the test, kept over the hops, went to and from a
+        // spilled register
+        int ch = __builtin_amdgcn_readfirstlane(chunks);
+        asm volatile("" : "+s"(ch));
+        if (ch == G * CPL)
             distances_impl<W, true>(m, w);
         else
             distances_impl<W, false>(m, w);
@@ -196,25 +203,43 @@ struct Searcher {
     }
 
     // first two pool positions at or after `from` whose entries are not
-    // expanded (-1 when missing): one ballot usually yields both
-    __device__ void next_two_unexpanded(int from, int &first, int &second) const
+    // expanded (-1 when missing), the first one's id and the second one's key
+    // and id (kMax and kEmpty when missing).  One ballot usually yields both;
+    // ids and keys come out of the registers that the scan has loaded (another
+    // read of LDS for them put two more of its latencies into every hop).
+    __device__ __forceinline__ void next_two_unexpanded(int from, int &first, int &second,
+                                                        uint32_t &id1, K &key2, uint32_t &id2) const
     {
         const int lane = beam::lane_id();
         const uint32_t *ai = ids(cur);
+        const K *ak = keys(cur);
         first = -1;
         second = -1;
+        id1 = beam::kEmpty;
+        key2 = KT::kMax;
+        id2 = beam::kEmpty;
         for (int b = from; b < cnt; b += 64) {
             const int j = b + lane;
-            const bool un = j < cnt && !(ai[j] & beam::kExpanded);
-            uint64_t bal = __ballot(un);
-            if (!bal) continue;
-            if (first < 0) {
-                first = b + __ffsll((unsigned long long)bal) - 1;
-                bal &= bal - 1;
-                if (!bal) continue;
+            uint32_t id = beam::kExpanded;
+            K key = KT::kMax;
+            if (j < cnt) {
+                id = ai[j];
+                key = ak[j];
             }
-            second = b + __ffsll((unsigned long long)bal) - 1;
-            return;
+            uint64_t bal = __ballot((int32_t)id >= 0);
+            if (first < 0 && bal) {
+                const int f = __ffsll((unsigned long long)bal) - 1;
+                first = b + f;
+                id1 = beam::readlane(id, f);
+                bal &= bal - 1;
+            }
+            if (bal) {
+                const int f = __ffsll((unsigned long long)bal) - 1;
+                second = b + f;
+                id2 = beam::readlane(id, f);
+                key2 = beam::readlane(key, f);
+                return;
+            }
         }
     }
 
@@ -234,8 +259,25 @@ struct Searcher {
                                                 int &pf_nb, K nkey, uint32_t nid, SearchResult &r)
     {
         const int lane = beam::lane_id();
-        const K *ak = keys(cur);
-        const uint32_t *ai = ids(cur);
+        const K *ak = pk0;
+        const uint32_t *ai = pi0;
+        // the new keys first: in the later part of a search most hops have none
+        // that a full pool takes (only keys below its last entry; a word below
+        // ~0: ids are below 2^31), and end here
+        bool valid = lane < m;
+        K kk = KT::kMax;
+        uint32_t ii = beam::kEmpty;
+        if (valid) {
+            kk = sk[lane];
+            ii = si[lane];
+        }
+        const uint64_t S = ((uint64_t)kk << 32) | ii;
+        if (cnt == Lq) {
+            const uint64_t last = ((uint64_t)ak[cnt - 1] << 32) | (ai[cnt - 1] & beam::kIdMask);
+            valid = valid && S < last;
+        }
+        const uint64_t vmask = __ballot(valid);
+        if (!vmask) return;
         // entries past cnt are read too (they lie inside the wave's LDS:
         // each pool array is followed by at least 64 entries of another) and
         // replaced by ~0; lane + 64 c < cnt is tested as lane < cnt - 64 c
@@ -248,23 +290,6 @@ struct Searcher {
             ex |= (id >> 31) << c;
             P[c] = lane < cnt - 64 * c ? w : ~0ull;
         }
-        bool valid = lane < m;
-        K kk = KT::kMax;
-        uint32_t ii = beam::kEmpty;
-        uint64_t S = ~0ull;
-        if (valid) {
-            kk = sk[lane];
-            ii = si[lane];
-            S = ((uint64_t)kk << 32) | ii;
-        }
-        // a full pool takes only keys below its last entry (a word below
-        // ~0: ids are below 2^31)
-        if (cnt == Lq) {
-            const uint64_t last = ((uint64_t)ak[cnt - 1] << 32) | (ai[cnt - 1] & beam::kIdMask);
-            valid = valid && S < last;
-        }
-        const uint64_t vmask = __ballot(valid);
-        if (!vmask) return;
         int ltc[CM];
 #pragma unroll
         for (int c = 0; c < CM; ++c) ltc[c] = 0;
@@ -317,10 +342,10 @@ struct Searcher {
             pf_nb = lane < R ? graph[(size_t)i0 * R + lane] : -1;
         }
         // the pool's reads are all done: the merged pool goes to the same
-        // buffer (keys(cur ^ 1) is keys(cur) for pools merged in place)
+        // buffer (pools of this size have one)
         beam::wave_sync();
-        K *bk = keys(cur ^ 1);
-        uint32_t *bi = ids(cur ^ 1);
+        K *bk = pk0;
+        uint32_t *bi = pi0;
         const int outn = __builtin_amdgcn_readfirstlane((cnt + mv < Lq) ? cnt + mv : Lq);
         const int fnew = pos + rank;
         if (valid && fnew < Lq) {
@@ -339,7 +364,6 @@ struct Searcher {
         const int oc = cursor + __popcll(__ballot(valid && pos <= cursor));
         cursor = __builtin_amdgcn_readfirstlane(f0 < oc ? f0 : oc);
         cnt = outn;
-        cur ^= 1;
         beam::wave_sync();
     }
 
@@ -349,15 +373,27 @@ struct Searcher {
                                           K nkey, uint32_t nid, SearchResult &r)
     {
         if constexpr (!F64) {
-            // the pools that pool_in_place gives one buffer
-            if (pool_cap <= 64) return merge_words<1>(m, Lq, cursor, pf_id, pf_nb, nkey, nid, r);
-            if (pool_cap <= 128) return merge_words<2>(m, Lq, cursor, pf_id, pf_nb, nkey, nid, r);
-            if (pool_cap <= 192) return merge_words<3>(m, Lq, cursor, pf_id, pf_nb, nkey, nid, r);
-            if (pool_cap <= 256) return merge_words<4>(m, Lq, cursor, pf_id, pf_nb, nkey, nid, r);
-            if (pool_cap <= 320) return merge_words<5>(m, Lq, cursor, pf_id, pf_nb, nkey, nid, r);
-            if (pool_cap <= 384) return merge_words<6>(m, Lq, cursor, pf_id, pf_nb, nkey, nid, r);
-            if (pool_cap <= 448) return merge_words<7>(m, Lq, cursor, pf_id, pf_nb, nkey, nid, r);
-            if (pool_cap <= 512) return merge_words<8>(m, Lq, cursor, pf_id, pf_nb, nkey, nid, r);
+            // the pools that pool_in_place gives one buffer.  A tree of
+            // compares of an opaque scalar: the compiler kept the chain's eight
+            // tests as masks over the hops, in spilled registers
+            int cap = __builtin_amdgcn_readfirstlane(pool_cap);
+            asm volatile("" : "+s"(cap));
+            if (cap <= 256) {
+                if (cap <= 128) {
+                    if (cap <= 64) return merge_words<1>(m, Lq, cursor, pf_id, pf_nb, nkey, nid, r);
+                    return merge_words<2>(m, Lq, cursor, pf_id, pf_nb, nkey, nid, r);
+                }
+                if (cap <= 192) return merge_words<3>(m, Lq, cursor, pf_id, pf_nb, nkey, nid, r);
+                return merge_words<4>(m, Lq, cursor, pf_id, pf_nb, nkey, nid, r);
+            }
+            if (cap <= 512) {
+                if (cap <= 384) {
+                    if (cap <= 320) return merge_words<5>(m, Lq, cursor, pf_id, pf_nb, nkey, nid, r);
+                    return merge_words<6>(m, Lq, cursor, pf_id, pf_nb, nkey, nid, r);
+                }
+                if (cap <= 448) return merge_words<7>(m, Lq, cursor, pf_id, pf_nb, nkey, nid, r);
+                return merge_words<8>(m, Lq, cursor, pf_id, pf_nb, nkey, nid, r);
+            }
         }
         merge_search(m, Lq, cursor, pf_id, pf_nb, nkey, nid, r);
     }
@@ -503,21 +539,16 @@ struct Searcher {
         int pf_nb = -1;
         for (;;) {
             int ppos, npos;
-            next_two_unexpanded(cursor, ppos, npos);
+            uint32_t p, nid;
+            K nkey;
+            next_two_unexpanded(cursor, ppos, npos, p, nkey, nid);
             if (ppos < 0 || stop(ppos, r, lost)) break;
             cursor = ppos;
-            const uint32_t p = ids(cur)[ppos] & beam::kIdMask;
             int nb = -1;
             if (p == pf_id)
                 nb = pf_nb;
             else if (lane < R)
                 nb = graph[(size_t)p * R + lane];
-            K nkey = KT::kMax;
-            uint32_t nid = beam::kEmpty;
-            if (npos >= 0) {
-                nkey = keys(cur)[npos];
-                nid = ids(cur)[npos] & beam::kIdMask;
-            }
             beam::wave_sync();
             if (lane == 0) {
                 ids(cur)[ppos] = p | beam::kExpanded;
@@ -584,21 +615,17 @@ struct Searcher {
             if (w == 0) {
                 int m = -1;
                 int ppos, npos;
-                next_two_unexpanded(cursor, ppos, npos);
+                uint32_t p;
+                next_two_unexpanded(cursor, ppos, npos, p, nkey, nid);
                 if (ppos >= 0) {
                     cursor = ppos;
-                    const uint32_t p = ids(cur)[ppos] & beam::kIdMask;
                     int nb = -1;
                     if (p == pf_id)
                         nb = pf_nb;
                     else if (lane < R)
                         nb = graph[(size_t)p * R + lane];
-                    nkey = KT::kMax;
-                    nid = beam::kEmpty;
                     pf_id = beam::kEmpty;
                     if (npos >= 0) {
-                        nkey = keys(cur)[npos];
-                        nid = ids(cur)[npos] & beam::kIdMask;
                         pf_id = nid;
                         pf_nb = lane < R ? graph[(size_t)nid * R + lane] : -1;
                     }
