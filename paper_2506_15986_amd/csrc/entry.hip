@@ -180,8 +180,11 @@ extern "C" ann_status ann_entry_select(const ann_entry_model *m, const float *qu
     const int blocks = (nq + 255) / 256;
     if (hub_search_supported(m->n_hubs, e, m->s, m->L_h)) {
         // narrow beams on a small hub graph: the register-pool search
-        s = hub_search_launch(m->hub_emb, m->n_hubs, e, m->hub_graph, m->s, qemb, nq, m->hub_entry,
-                              m->L_h, best, d2, nullptr, nullptr, 0, st);
+        return hub_search_launch(m->hub_emb, m->n_hubs, e, m->hub_graph, m->s, qemb, nq, m->hub_entry,
+                                 m->L_h, best, d2, nullptr, nullptr, 0,
+                                 HubEntry{m->hub_ids, m->theta, m->medoid, entry_ids, entry_score,
+                                          best_hub},
+                                 st);
     } else {
         hipLaunchKernelGGL(fill_kl_kernel, dim3(blocks), dim3(256), 0, st, kk, LL, nq, 1, m->L_h);
         ANN_LAUNCHED();

@@ -69,6 +69,7 @@ struct HubArgs {
     int32_t *trace;
     int trace_cap;
     int vis_words;   // bitset words per wavefront
+    HubEntry entry;  // ids NULL: not wanted
 };
 
 // LDS of one wavefront: 64 merge words, 64 staged ids, the visited bitset
@@ -228,6 +229,13 @@ __global__ void __launch_bounds__(256) hub_search_kernel(HubArgs a)
     if (lane == 0) {
         a.best[qi] = (int32_t)((uint32_t)P & 0xffffu);
         a.best_d2[qi] = __uint_as_float((uint32_t)(P >> 32));
+        if (a.entry.ids) {
+            const uint32_t b = (uint32_t)P & 0xffffu;
+            const float cosv = __builtin_fmaf(-0.5f, __uint_as_float((uint32_t)(P >> 32)), 1.0f);
+            a.entry.ids[qi] = cosv < a.entry.theta ? a.entry.medoid : a.entry.hub_ids[b];
+            if (a.entry.score) a.entry.score[qi] = cosv;
+            if (a.entry.best_hub) a.entry.best_hub[qi] = (int32_t)b;
+        }
         if (a.stats) {
             a.stats[2 * qi] = ndc;
             a.stats[2 * qi + 1] = hops;
@@ -257,10 +265,10 @@ bool hub_search_supported(int n_hubs, int dim, int s, int L)
 ann_status hub_search_launch(const float *emb, int n_hubs, int dim, const int32_t *graph, int s,
                              const float *qemb, int nq, int start, int L, int32_t *best,
                              float *best_d2, int32_t *stats, int32_t *trace, int trace_cap,
-                             hipStream_t st)
+                             const HubEntry &entry, hipStream_t st)
 {
     HubArgs a{emb, n_hubs, dim, graph, s, qemb, nq, start, L, best, best_d2, stats,
-              trace, trace ? trace_cap : 0, (n_hubs + 31) / 32};
+              trace, trace ? trace_cap : 0, (n_hubs + 31) / 32, entry};
     const size_t lds = 4 * hub_wave_lds(a.vis_words);
     const dim3 grid((unsigned)((nq + 3) / 4));
     const int T = (dim / 4 + 3) / 4;
@@ -293,5 +301,5 @@ extern "C" ann_status ann_hub_search(const float *emb, int32_t n_hubs, int32_t d
     ANN_REQUIRE(trace == nullptr || trace_cap >= 1, "trace_cap must be >= 1 with a trace buffer");
     if (nq == 0) return ANN_OK;
     return hub_search_launch(emb, n_hubs, dim, graph, s, qemb, nq, start, L, best, best_d2, stats,
-                             trace, trace_cap, static_cast<hipStream_t>(stream));
+                             trace, trace_cap, HubEntry{}, static_cast<hipStream_t>(stream));
 }

@@ -42,10 +42,15 @@ __global__ void __launch_bounds__(256) search_kernel(SearchArgs a)
     S s;
     s.setup(smem + (size_t)wave * a.wave_lds, a.pool_cap, a.visited_log2, a.filter, a.n, a.base,
             a.dim, a.graph, a.R);
+    int own = a.counter ? -1 : (int)(blockIdx.x * (blockDim.x >> 6)) + wave;
     for (;;) {
-        int slot = 0;
-        if (lane == 0) slot = (int)atomicAdd(a.counter, 1u);
-        slot = __shfl(slot, 0);
+        int slot = own;
+        if (own < 0) {
+            if (lane == 0) slot = (int)atomicAdd(a.counter, 1u);
+            slot = __shfl(slot, 0);
+        } else {
+            own = 0x7fffffff;
+        }
         if (slot >= a.nq) break;
         const int qi = a.order ? a.order[slot] : slot;
         if (qi < 0 || qi >= a.nq) continue;
@@ -159,26 +164,47 @@ __global__ void __launch_bounds__(1024) order_sort_kernel(const uint32_t *key, i
     for (int q = t; q < nq; q += 1024) order[atomicAdd(&hist[key[q]], 1u)] = q;
 }
 
+ann_status order_queries(SearchArgs &a, hipStream_t st)
+{
+    hipLaunchKernelGGL(order_key_kernel, dim3((a.nq + 3) / 4), dim3(256), 0, st, a.base, a.n, a.dim,
+                       a.queries, a.nq, a.entry, a.medoid, a.L, a.key_buf);
+    ANN_LAUNCHED();
+    hipLaunchKernelGGL(order_sort_kernel, dim3(1), dim3(1024), 0, st, a.key_buf, a.nq, a.order_buf,
+                       a.counter);
+    ANN_LAUNCHED();
+    a.order = a.order_buf;
+    return ANN_OK;
+}
+
 template <int G, int CPL, bool F64, int FILT>
-ann_status launch_one(const SearchArgs &a, int blocks, int wpb, hipStream_t st)
+ann_status launch_one(SearchArgs a, int blocks, int wpb, hipStream_t st)
 {
     auto kern = search_kernel<G, CPL, F64, FILT>;
     size_t lds = (size_t)wpb * a.wave_lds;
     if (lds > 65536) ANN_HIP(hipFuncSetAttribute((const void *)kern,
                                                  hipFuncAttributeMaxDynamicSharedMemorySize,
                                                  (int)lds));
+    const int need = (a.nq + wpb - 1) / wpb;
+    bool all = false;
     if (blocks <= 0) {
         int per_cu = 0;
         ANN_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, 64 * wpb, lds));
         if (per_cu < 1) return fail(ANN_ENOTSUP, "search plan does not fit on a CU (%zu B LDS)", lds);
         blocks = per_cu * device_cus();
+        all = need <= blocks;
     }
-    int need = (a.nq + wpb - 1) / wpb;
     if (blocks > need) blocks = need;
     if (blocks < 1) blocks = 1;
-    if (!a.order) {   // with the query-order pre-pass its sort kernel zeroed it
-        ann_status rs = reset_work_counter(a.counter, st);
-        if (rs != ANN_OK) return rs;
+    if (all && !a.order_buf) {
+        // every query starts at once: nothing to count (a launch of 5 us before
+        // a search of 100; where an order is asked for, its sort zeroes the
+        // counter, and the order is worth its 9 us even then: 257 mixed queries
+        // 915 us with it, 933 without)
+        a.counter = nullptr;
+    } else {
+        // the order's sort zeroes the work counter
+        const ann_status os = a.order_buf ? order_queries(a, st) : reset_work_counter(a.counter, st);
+        if (os != ANN_OK) return os;
     }
     hipLaunchKernelGGL(kern, dim3(blocks), dim3(64 * wpb), lds, st, a);
     ANN_LAUNCHED();
@@ -308,20 +334,19 @@ ann_status search_launch(const float *base, int64_t n, int32_t dim, const int32_
         if (fs != ANN_OK) return fs;
     }
     a.wave_lds = wave_lds_bytes(p.pool_cap, a.filter, p.fp64 != 0, dim);
-    a.order = nullptr;
     if (widest_first && p.query_order == ANN_ORDER_WIDEST_FIRST && nq > 1) {
         // the workspace after the counter: order, keys
         Carve cv{reinterpret_cast<unsigned char *>(counter) + 256};
-        int32_t *order = cv.take<int32_t>((size_t)nq);
-        uint32_t *key = cv.take<uint32_t>((size_t)nq);
-        hipLaunchKernelGGL(order_key_kernel, dim3((nq + 3) / 4), dim3(256), 0, st, base, n, dim,
-                           queries, nq, entry_ids, medoid, L, key);
-        ANN_LAUNCHED();
-        hipLaunchKernelGGL(order_sort_kernel, dim3(1), dim3(1024), 0, st, key, nq, order, counter);
-        ANN_LAUNCHED();
-        a.order = order;
+        a.order_buf = cv.take<int32_t>((size_t)nq);
+        a.key_buf = cv.take<uint32_t>((size_t)nq);
     }
-    if (p.waves_per_query > 1) return launch_search_mw(a, p.waves_per_query, p.blocks, st);
+    if (p.waves_per_query > 1) {
+        if (a.order_buf) {
+            const ann_status os = order_queries(a, st);
+            if (os != ANN_OK) return os;
+        }
+        return launch_search_mw(a, p.waves_per_query, p.blocks, st);
+    }
     if (p.fp64) return dispatch<true>(a, p.group, p.blocks, p.waves_per_block, st);
     return dispatch<false>(a, p.group, p.blocks, p.waves_per_block, st);
 }

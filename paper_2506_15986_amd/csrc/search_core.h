@@ -27,8 +27,10 @@ struct SearchArgs {
     int pool_cap;
     int visited_log2;
     beam::FilterShape filter;
-    uint32_t *counter;
+    uint32_t *counter;      // NULL: every wavefront takes the query of its own number
     const int32_t *order;   // NULL, or the order in which the queries are taken
+    int32_t *order_buf;     // NULL: taken as given; else where to put an order and its keys
+    uint32_t *key_buf;
     size_t wave_lds;
 };
 
