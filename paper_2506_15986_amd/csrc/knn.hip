@@ -1112,6 +1112,7 @@ ann_status run_f16(KnnArgs f, int *flag, unsigned char *p, hipStream_t st)
         a.bE = bE;
         a.qV = shared ? bV : qV;
         a.qE = shared ? bE : qE;
+        a.bits = bits;
         a.n = n;
         a.rows = left;
         a.dpad = dp;
@@ -1168,7 +1169,7 @@ ann_status run_f16(KnnArgs f, int *flag, unsigned char *p, hipStream_t st)
         ANN_HIP(hipStreamSynchronize(st));
         left = (int32_t)h[1 + level];
         f.row_list = todo[level];
-        if (h[0] >= 0x7f800000u) break;      // values that are not finite: the plain engine
+        if (h[0] >= f16::kNotFinite) break;  // values that are not finite: the plain engine
     }
     if (left > 0) {
         f.rows = left;

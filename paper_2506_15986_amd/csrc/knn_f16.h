@@ -40,6 +40,7 @@ constexpr int kMaxSample = 4096; // columns the first thresholds are taken from
 constexpr int kRing = 512;       // candidates a wavefront holds back in LDS before writing them out
 constexpr int kRsrcWord3 = 0x00020000;  // buffer resource word 3 (raw, 32-bit data)
 constexpr int kWaitVmcnt0 = 0x0F70;   // s_waitcnt vmcnt(0), the other counters left alone
+constexpr uint32_t kNotFinite = 0x7f800000u;   // a spread from here on: infinities, NaN, FP32 overflow
 
 // order-preserving image of a float
 __device__ inline uint32_t ord(float f)
@@ -274,6 +275,7 @@ struct Args {
     const _Float16 *bh, *bl;   // columns, n x dpad
     const _Float16 *qh, *ql;   // rows, rows x dpad
     const float *bV, *bE, *qV, *qE;
+    const uint32_t *bits;      // the data's spread
     int64_t n, rows;
     int dpad;
     int K;                     // neighbours that a row's threshold guards
@@ -439,6 +441,12 @@ constexpr size_t tile_lds()
 // first two tiles alone were 64 KB of stores per wavefront) and is cut several
 // times: 50,001 x 96, K = 64 10.5 ms against 2.3 ms.
 //
+// Data whose spread is not finite ends here at once (the host learns of it with
+// the pass's results and takes the plain engine): its products may be
+// infinite, and the lists' bounds hold for finite values only.  The bound of a
+// row that takes no columns, past the last or given up, is NaN: no value
+// passes it, an infinite one neither.
+//
 // Measured against the plain FP64 engine, whole calls: ann_build_graph of
 // 50,001 x 96 (K = 64) 113.5 -> 8.0 ms, of which this kernel 109 -> 2.6 ms; the
 // 10 nearest of 1,000 queries among 150,000 x 960 526 -> 1.3 ms (this kernel
@@ -449,6 +457,7 @@ tile_kernel(Args a)
 {
     constexpr bool EST = CAPW == 0;
     constexpr int CAP = 64 * CAPW;
+    if (*a.bits >= kNotFinite) return;
     constexpr int RB = CAPW <= 4 ? 4 : CAPW <= 8 ? 2 : 1;         // rows cut together
     constexpr int AS = kRowsWG * 8 / 256, BS = kCols * 8 / 256;   // 16-byte slots per thread
     extern __shared__ __align__(16) unsigned char dyn[];
@@ -489,10 +498,10 @@ tile_kernel(Args a)
         return c_begin + (int64_t)j * kCols;
     };
     const int nch = (a.dpad + kDk - 1) / kDk;
-    const float big = 3.0e38f, inf = __builtin_inff();
+    const float big = 3.0e38f, inf = __builtin_inff(), none = __builtin_nanf("");
     {
         const int64_t g = row0 + t;
-        r_rt[t] = g < a.rows ? (a.first ? a.qV[g] - a.first[g] : -big) : inf;
+        r_rt[t] = g < a.rows ? (a.first ? a.qV[g] - a.first[g] : -big) : none;
         r_V[t] = g < a.rows ? a.qV[g] : 0.f;
         r_cnt[t] = 0;
     }
@@ -591,7 +600,7 @@ tile_kernel(Args a)
             if (lane == 0 && c[b] > 0) {
                 const bool fits = c[b] <= most;
                 r_cnt[r[b]] = fits ? c[b] : -1;
-                if (more) r_rt[r[b]] = fits ? r_V[r[b]] - th[b] : inf;
+                if (more) r_rt[r[b]] = fits ? r_V[r[b]] - th[b] : none;
             }
         knn::wsync();
     };
@@ -798,7 +807,7 @@ __global__ void __launch_bounds__(64) final_kernel(FinalArgs a)
     // the slices' counts, one per lane, and their places; then the words,
     // sixteen lanes to a slice, four slices' loads in flight
     const int mine = lane < a.slices ? a.cnt[g * a.slices + lane] : 0;
-    bool ok = *a.bits < 0x7f800000u && !__builtin_amdgcn_ballot_w64(mine < 0);
+    bool ok = *a.bits < kNotFinite && !__builtin_amdgcn_ballot_w64(mine < 0);
     int end = mine;
     for (int o = 1; o < 64; o <<= 1) {
         const int other = __shfl_up(end, o);

@@ -256,6 +256,37 @@ def test_build_graph_small_alpha_variants():
         assert (g.cpu().numpy() == ref).all()
 
 
+@pytest.mark.parametrize("n,d,k,kind", [
+    (1_500, 8, 10, "infinite query"),     # no first thresholds: lists that fill
+    (1_500, 8, 10, "overflow"),           # finite, but x - c is beyond FP32
+    (12_000, 16, 1000, "infinite query"),
+    (5_000, 16, 10, "infinite query"),    # first thresholds
+    (5_000, 16, 10, "overflow"),
+    (1_500, 8, 10, "infinite base"),
+])
+def test_knn_of_values_beyond_fp16_products_matches_oracle(n, d, k, kind):
+    # large finite values (few bits, so that FP64 sums are exact) beside an
+    # infinity or of both signs near the largest float: products that are
+    # infinite in the FP16 estimates, distances that FP64 tells apart
+    r = np.random.default_rng(n + d)
+    base = (r.integers(1, 256, size=(n, d)) * 2.0 ** 100).astype(np.float32)
+    q = (r.integers(1, 256, size=(40, d)) * 2.0 ** 100).astype(np.float32)
+    if kind == "infinite query":
+        q[::3, 1] = np.inf
+    elif kind == "infinite base":
+        base[::7, 2] = np.inf
+    else:
+        base = (r.integers(192, 256, size=(n, d)) * 2.0 ** 120).astype(np.float32)
+        q = -base[:40]
+    say("case: kNN beyond FP16 products n=%d d=%d k=%d %s" % (n, d, k, kind))
+    ids, dist = _ann().ann_gt_knn(_dev(base), _dev(q), k)
+    torch.cuda.synchronize()
+    ref_ids, ref_d2 = oracle.knn(base, q, k)
+    assert (ids.cpu().numpy() == ref_ids).all()
+    with np.errstate(over="ignore"):
+        assert (dist.cpu().numpy() == ref_d2.astype(np.float32)).all()
+
+
 def _repair_points(which):
     r = np.random.default_rng(17)
     if which == "equal points":
