@@ -1288,7 +1288,7 @@ namespace {
 // taken
 int half_padded(int dim, int nh)
 {
-    if (dim % 4 || dim > HB_MAX_DIM || nh > HB_MAX_NH) return 0;
+    if (dim < 4 || dim % 4 || dim > HB_MAX_DIM || nh > HB_MAX_NH) return 0;
     const int per = 16 * lds_tiles(frags_of(dim));
     return (nh + per - 1) / per * per;
 }

@@ -887,7 +887,8 @@ struct Plan {
 Plan plan(int64_t n, int64_t rows, int K, bool one_slice)
 {
     Plan p{};
-    p.Kp = K + 1;          // room for the row's own column
+    if (n < 1) n = 1;      // a plan for empty inputs too, as f16::plan
+    p.Kp = (K > 0 ? K : 0) + 1;     // room for the row's own column
     // a row's buffer holds its best Kp and at least one more tile; below 512
     // entries it also holds Kp more, so that a row is sorted at most once per
     // Kp new candidates
@@ -948,7 +949,7 @@ ann_status launch_tiles(const Args &a, hipStream_t st)
 size_t knn_cap(int K)
 {
     size_t c = 2;
-    while (c < (size_t)(K + F_BN)) c <<= 1;
+    while (c < (size_t)((K > 0 ? K : 0) + F_BN)) c <<= 1;
     return c;
 }
 

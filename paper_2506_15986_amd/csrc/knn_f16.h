@@ -934,10 +934,13 @@ struct Plan {
 // a group and a half; the estimates use the row buffers' memory.  0: too few
 // columns to gain from it.
 // max_slices: 0 = no other limit.  grouped: a group's columns are the sample.
+// Empty inputs get a plan too (sizes are asked for before a call refuses them).
 inline Plan plan(int64_t n, int64_t rows, int K, int cus, int64_t max_slices, bool grouped)
 {
     Plan p{};
-    p.Kp = K + 1;     // room for the row's own column
+    if (n < 1) n = 1;
+    if (rows < 1) rows = 1;
+    p.Kp = (K > 0 ? K : 0) + 1;     // room for the row's own column
     const int need = 2 * p.Kp + kCols;
     p.cap = need <= 256 ? 256 : need <= 512 ? 512 : p.Kp <= 512 ? 1024 : 2048;
     const int64_t blocks = (rows + kRowsWG - 1) / kRowsWG;

@@ -3,6 +3,8 @@ rejects bad arguments on the host before touching the device (CPU only)."""
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -106,6 +108,55 @@ def test_default_plan_and_workspace():
     assert ann.workspace_size("search", 1000, 32, 1) == 256
     assert ann.workspace_size("search", 1000, 32, 10) >= 256 + 2 * 40
     assert ann.workspace_size("search", 1000, 32, 100000) >= 256 + 2 * 400000
+
+
+def _size_calls(name, *values):
+    """Calls a size function with all combinations of the values, in a process of its own."""
+    code = """
+import ctypes, itertools, sys
+lib = ctypes.CDLL(%r)
+f = getattr(lib, %r)
+f.restype = ctypes.c_size_t
+for v in itertools.product(*%r):
+    print(v, file=sys.stderr, flush=True)
+    f(*[ctypes.c_int64(x) for x in v])
+""" % (LIB, name, values)
+    return subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=60)
+
+
+_EMPTY = [-1, 0, 1, 70]
+
+
+@pytest.mark.parametrize("name,values", [
+    ("ann_workspace_size", [range(0, 8), _EMPTY, _EMPTY, _EMPTY, [-70, -49, -33, -1, 0, 1, 70]]),
+    ("ann_navgraph_workspace_size", [_EMPTY] * 3),
+    ("ann_build_graph_partitioned_workspace_size", [_EMPTY] * 6),
+    ("ann_group_candidates_workspace_size", [_EMPTY] * 4),
+    ("ann_graph_from_candidates_workspace_size", [_EMPTY] * 3),
+    ("ann_merge_candidates_workspace_size", []),
+    ("ann_select_hubs_hbkm_workspace_size", [_EMPTY] * 4),
+    ("ann_train_workspace_size", [_EMPTY] * 6),
+    ("ann_train_hub_workspace_size", [_EMPTY] * 7),
+    ("ann_hop_table_workspace_size", [_EMPTY]),
+    ("ann_make_queues_workspace_size", [_EMPTY] * 2),
+    ("ann_autotune_workspace_size", [_EMPTY] * 4),
+])
+def test_sizes_of_empty_inputs(lib, name, values):
+    p = _size_calls(name, *[list(v) for v in values])
+    assert p.returncode == 0, (name, p.returncode, p.stderr.strip().splitlines()[-1:])
+
+
+def test_knn_without_queries_is_valid(lib):
+    code = """
+import ctypes
+from paper_2506_15986_amd import ann
+nb = ann.workspace_size("gt_knn", 1000, 32, 0, 10)
+p = ctypes.c_void_p(0x10000)         # never dereferenced
+s = ann._lib.ann_gt_knn(p, 1000, 32, None, 0, 10, 0, None, None, p, nb, None)
+raise SystemExit(0 if nb > 0 and s == ann.ANN_OK else 1)
+"""
+    p = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=120)
+    assert p.returncode == 0, (p.returncode, p.stderr[-400:])
 
 
 def test_kernel_names_unique_across_translation_units():
