@@ -172,8 +172,8 @@ inline int table_log2(int L, int R, int rows)
 // queries whose rows are searched together: the lists stay bounded
 inline int chunk_queries(int nq, int M)
 {
-    const int c = LB_ROWS / M < 1 ? 1 : LB_ROWS / M;
-    return nq < c ? nq : c;
+    const int c = M > 1 ? LB_ROWS / M : LB_ROWS;   // M < 1: refused, but its size is asked for
+    return nq < 1 ? 0 : nq < c ? nq : c < 1 ? 1 : c;
 }
 
 template <int G, int CPL>

@@ -140,6 +140,7 @@ _EMPTY = [-1, 0, 1, 70]
     ("ann_hop_table_workspace_size", [_EMPTY]),
     ("ann_make_queues_workspace_size", [_EMPTY] * 2),
     ("ann_autotune_workspace_size", [_EMPTY] * 4),
+    ("ann_labels_workspace_size", [_EMPTY] * 3),
 ])
 def test_sizes_of_empty_inputs(lib, name, values):
     p = _size_calls(name, *[list(v) for v in values])
@@ -154,6 +155,23 @@ nb = ann.workspace_size("gt_knn", 1000, 32, 0, 10)
 p = ctypes.c_void_p(0x10000)         # never dereferenced
 s = ann._lib.ann_gt_knn(p, 1000, 32, None, 0, 10, 0, None, None, p, nb, None)
 raise SystemExit(0 if nb > 0 and s == ann.ANN_OK else 1)
+"""
+    p = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=120)
+    assert p.returncode == 0, (p.returncode, p.stderr[-400:])
+
+
+def test_labels_without_candidates_are_refused(lib):
+    code = """
+import types
+import torch
+from paper_2506_15986_amd import ann
+z = lambda *s: torch.zeros(s, dtype=torch.float32)
+i = lambda *s: torch.zeros(s, dtype=torch.int32)
+try:
+    ann.ann_make_labels(z(10, 8), i(10, 4), z(3, 8), i(3, 2), 1, i(3, 0), i(4), [4], stream=types.SimpleNamespace(cuda_stream=0))
+except ann.AnnError:
+    raise SystemExit(0)
+raise SystemExit(1)
 """
     p = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=120)
     assert p.returncode == 0, (p.returncode, p.stderr[-400:])
