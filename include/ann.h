@@ -443,7 +443,9 @@ size_t ann_train_workspace_size(int32_t batch, int32_t n_hubs, int32_t din_q, in
  * *loss (device FP32), the embeddings to q_emb / h_emb when non-NULL, and
  * when step >= 1 applies Adam (beta1 0.9, beta2 0.999, eps 1e-8, bias
  * correction with t = step) to both towers and refreshes their BF16 copies.
- * step == 0 computes gradients only.  hub_in_grad (n_hubs x din_h, device,
+ * step == 0 computes gradients only.  Towers may share parameters, gradients
+ * or moments: the query tower's are then written first and the hub tower's
+ * after them.  hub_in_grad (n_hubs x din_h, device,
  * or NULL) receives dL/d hub_in (the input's BF16 rounding taken as the
  * identity), for an upstream module such as the fusion embedding. */
 ann_status ann_train_step(ann_tower *query_tower, ann_tower *hub_tower,

@@ -1015,6 +1015,42 @@ GradArgs grad_args(const ann_tower &w, const ann_tower_grads &gr, const ann_adam
 
 inline int row_blocks(int rows) { return (rows + 15) / 16; }
 
+// Both towers' gradients and updates are written in one launch, so what one
+// tower writes must be apart from what the other writes; towers that share
+// parameters, gradients or moments are updated one after the other, in the
+// generic step.
+bool written_apart(const GradArgs &a, const GradArgs &b, int step)
+{
+    struct Range {
+        uintptr_t begin, end;
+    };
+    auto ranges = [&](const GradArgs &x, Range *r) {
+        const size_t n[4] = {(size_t)x.hidden * x.din, (size_t)x.hidden, (size_t)x.dout * x.hidden, (size_t)x.dout};
+        int c = 0;
+        auto add = [&](const void *p, size_t bytes) {
+            r[c++] = Range{reinterpret_cast<uintptr_t>(p), reinterpret_cast<uintptr_t>(p) + bytes};
+        };
+        for (int i = 0; i < 4; ++i) {
+            add(x.g[i], n[i] * 4);
+            if (step < 1) continue;
+            add(x.p[i], n[i] * 4);
+            add(x.m[i], n[i] * 4);
+            add(x.v[i], n[i] * 4);
+        }
+        if (step > 0) {
+            add(x.W1b, n[0] * 2);
+            add(x.W2b, n[2] * 2);
+        }
+        return c;
+    };
+    Range ra[18], rb[18];
+    const int na = ranges(a, ra), nb = ranges(b, rb);
+    for (int i = 0; i < na; ++i)
+        for (int j = 0; j < nb; ++j)
+            if (ra[i].begin < rb[j].end && rb[j].begin < ra[i].end) return false;
+    return true;
+}
+
 // One training step around a loss: both towers' forward, `loss` (which
 // enqueues the logits, the loss rows and the embeddings' gradients b.de), both
 // backwards, `inputs` (work that needs the old weights), Adam when step >= 1
@@ -1026,7 +1062,9 @@ ann_status train_towers(ann_tower &qt, ann_tower &ht, const ann_tower_grads &qg,
                         const int32_t *ih, int rh, float lr, int step, const float *loss_rows, int loss_count,
                         float *mean_loss, Loss loss, Inputs inputs, hipStream_t st)
 {
-    if (fused_ok(qt, xq) && fused_ok(ht, xh)) {
+    GradPair g{{grad_args(qt, qg, qa, bq, rq), grad_args(ht, hg, ha, bh, rh)},
+               step > 0 ? adam_step(step, lr) : AdamStep{}, step, loss_rows, loss_count, mean_loss};
+    if (fused_ok(qt, xq) && fused_ok(ht, xh) && written_apart(g.t[0], g.t[1], step)) {
         TowerPair p{{tower_args(qt, bq, xq, iq, rq), tower_args(ht, bh, xh, ih, rh)}, row_blocks(rq)};
         const dim3 grid((unsigned)(p.blocks0 + row_blocks(rh)));
         const int din = qt.din > ht.din ? qt.din : ht.din;
@@ -1037,8 +1075,6 @@ ann_status train_towers(ann_tower &qt, ann_tower &ht, const ann_tower_grads &qg,
         hipLaunchKernelGGL(tower_bwd_rows_kernel, grid, dim3(256), (size_t)32 * (qt.dout + 8), st, p);
         ANN_LAUNCHED();
         TRY(inputs());
-        GradPair g{{grad_args(qt, qg, qa, bq, rq), grad_args(ht, hg, ha, bh, rh)},
-                   step > 0 ? adam_step(step, lr) : AdamStep{}, step, loss_rows, loss_count, mean_loss};
         hipLaunchKernelGGL(tower_grad_kernel, dim3((unsigned)(g.t[0].blocks + g.t[1].blocks + 1)), dim3(256),
                            0, st, g);
         ANN_LAUNCHED();

@@ -682,6 +682,37 @@ def test_labels_overflowing_the_visited_table_are_searched_again():
     assert (lab == ref_lab).all()
 
 
+@pytest.mark.parametrize("shared", ["tower", "second weights", "moments"])
+def test_training_step_of_towers_that_share(shared):
+    # towers that share what a step writes are updated one after the other:
+    # aligned rows give the same bits as rows that take the generic kernels
+    ann = _ann()
+    say("case: towers that share %s" % shared)
+    r = np.random.default_rng(3)
+    B, nh, d, hidden, dout = 200, 90, 64, 128, 64
+    mk = lambda *s: (r.normal(size=s) / np.sqrt(s[-1])).astype(np.float32)
+    wq, wh = (mk(hidden, d), mk(hidden), mk(dout, hidden), mk(dout)), (mk(hidden, d), mk(hidden), mk(dout, hidden), mk(dout))
+    x, hub_in = _dev(mk(2 * B, d)), _dev(mk(nh, d))
+    idx = _dev(r.permutation(2 * B)[:B].astype(np.int32))
+    lab = _dev(r.integers(0, nh, 2 * B).astype(np.int32))
+    got = []
+    for off in (0, 1):
+        qt = ann.Tower(*wq)
+        ht = qt if shared == "tower" else ann.Tower(*wh)
+        if shared == "second weights":
+            ht.W2, ht.W2b, ht.b2 = qt.W2, qt.W2b, qt.b2
+        elif shared == "moments":
+            ht.m[0], ht.v[0] = qt.m[0], qt.v[0]
+        xo, ho = _offset_copy(x, off), _offset_copy(hub_in, off)
+        outs = []
+        for step in (0, 1, 2, 3):
+            loss, qe, he = ann.ann_train_step(qt, ht, xo, idx, lab, ho, 0.07, 1e-2, step, want_emb=True)
+            outs += [loss, qe, he] + [t.clone() for t in qt.g + ht.g]
+        outs += qt.params() + ht.params() + qt.m + qt.v + ht.m + ht.v + [qt.W1b, qt.W2b, ht.W1b, ht.W2b]
+        got.append([t.cpu().numpy().tobytes() for t in outs])
+    assert got[0] == got[1]
+
+
 @pytest.mark.parametrize("case", ["tables", "chunks"])
 def test_labels_row_lists(case):
     ann = _ann()
