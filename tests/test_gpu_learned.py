@@ -713,6 +713,33 @@ def test_training_step_of_towers_that_share(shared):
     assert got[0] == got[1]
 
 
+def test_training_step_of_more_rows_than_a_launch_dimension_holds():
+    # 8 * 65,535 = 524,280 rows of the FP32 products fill a launch's second
+    # dimension; the rows past them count too.  A batch that holds every query
+    # twice has the loss and the gradients of the batch that holds it once.
+    # FP32 sums of 600,000 terms: random rounding gives 5e-5 of a gradient's
+    # norm, rows left out 0.1; the bound lies between
+    ann = _ann()
+    B, nh, d = 600_000, 9, 8
+    say("case: training step, batch %d" % B)
+    r = np.random.default_rng(11)
+    mk = lambda *s: (r.normal(size=s) / np.sqrt(s[-1])).astype(np.float32)
+    wq, wh = (mk(16, d), mk(16), mk(16, 16), mk(16)), (mk(16, d), mk(16), mk(16, 16), mk(16))
+    x, hub_in = _dev(mk(B // 2, d)), _dev(mk(nh, d))
+    lab = _dev(r.integers(0, nh, B // 2).astype(np.int32))
+    once = torch.arange(B // 2, dtype=torch.int32, device="cuda")
+    got = []
+    for idx in (once, torch.cat([once, once])):
+        qt, ht = ann.Tower(*wq), ann.Tower(*wh)
+        loss, qe, he = ann.ann_train_step(qt, ht, x, idx, lab, hub_in, 0.1, 1e-2, 0, want_emb=True)
+        s = qe.double() @ he.double().T / 0.1
+        ref = (torch.logsumexp(s, 1) - s.gather(1, lab[idx.long()].long()[:, None])[:, 0]).mean()
+        assert abs(float(loss) - float(ref)) <= 1e-3 * abs(float(ref))
+        got.append([t.double() for t in qt.g + ht.g])
+    for a, b in zip(*got):
+        assert float((a - b).norm()) <= 1e-2 * float(a.norm())
+
+
 @pytest.mark.parametrize("case", ["tables", "chunks"])
 def test_labels_row_lists(case):
     ann = _ann()
