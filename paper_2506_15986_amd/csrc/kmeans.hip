@@ -398,7 +398,7 @@ struct StepState {
 
 struct OpenPoint {               // up to four centroids, 0xffff for none
     int32_t point;
-    uint32_t c01, c23;
+    uint16_t c[4];
     uint32_t pad;
 };
 
@@ -572,12 +572,10 @@ __global__ void __launch_bounds__(256, KS <= 8 ? 3 : 1) assign_half_kernel(HalfA
                 int at = 0;
                 if ((lane & 15) == 0) at = atomicAdd(&s_n[0], 1);
                 at = __shfl(at, g16);
-                uint16_t *oc = reinterpret_cast<uint16_t *>(&s_open[at].c01);
-                if ((lane & 15) == 0) {
-                    s_open[at].point = (int32_t)p;
-                    s_open[at].c01 = s_open[at].c23 = 0xffffffffu;
-                }
-                if (cand) oc[__popc(cb & ((1u << (lane & 15)) - 1u))] = (uint16_t)c;
+                if ((lane & 15) == 0) s_open[at].point = (int32_t)p;
+                // places 0 .. m - 1 and m .. 3: each written once
+                if (cand) s_open[at].c[__popc(cb & ((1u << (lane & 15)) - 1u))] = (uint16_t)c;
+                if ((lane & 15) >= m && (lane & 15) < 4) s_open[at].c[lane & 15] = 0xffff;
             } else if ((lane & 15) == 0) {
                 s_left[atomicAdd(&s_n[1], 1)] = make_int2((int)p, (int)(cb | (~nb & 0xffffu)));
             }
@@ -600,8 +598,8 @@ __global__ void __launch_bounds__(256) open_kernel(const float *base, int dim, b
     const int sub = threadIdx.x & 3;
     // every lane of a group of four takes part in the exchange below
     for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < total; e += gridDim.x * blockDim.x) {
-        const OpenPoint o = open[e >> 2];
-        int c = (int)(((sub & 2 ? o.c23 : o.c01) >> (16 * (sub & 1))) & 0xffffu);
+        const OpenPoint &o = open[e >> 2];
+        int c = o.c[sub];
         double v = __longlong_as_double(0x7ff0000000000000ll);
         if (c != 0xffff) v = d2_to(base + (int64_t)o.point * dim, mu + (int64_t)c * dim, dim, vec4);
         for (int x = 1; x < 4; x <<= 1) {

@@ -155,6 +155,28 @@ def test_hub_features_match_oracle():
     assert np.allclose(f.cpu().numpy(), ref, rtol=0, atol=1e-4)
 
 
+@pytest.mark.parametrize("m", [2, 3, 4, 5])
+def test_select_hubs_equal_centroids(m):
+    # every centroid starts m times over, in lanes of their own: a point has m
+    # open candidates (up to four are decided in one list, five go to the
+    # class search) and takes the first
+    r = np.random.default_rng(m)
+    n, dim, places = 4000, 64, 12
+    base = r.integers(0, 256, size=(n, dim)).astype(np.float32)
+    init = r.choice(n, m * places, replace=False).astype(np.int32)
+    for j in range(m):
+        base[init[j * places:(j + 1) * places]] = base[init[:places]]
+    say("case: select_hubs, %d equal centroids" % m)
+    for iters in (1, 3):
+        ref = oracle.kmeans_hubs(base, m * places, iters, init)
+        hub, cen, asg, steps = _ann().ann_select_hubs(_dev(base), m * places, iters, _dev(init))
+        torch.cuda.synchronize()
+        assert steps == ref["steps"]
+        assert (asg.cpu().numpy() == ref["assign"]).all()
+        assert (cen.cpu().numpy() == ref["centroids"]).all()
+        assert (hub.cpu().numpy() == ref["hub_ids"]).all()
+
+
 @pytest.mark.parametrize("n,dim,R,h,wcap", [
     (900, 6, 64, 3, 1),       # the hub alone; rows that are no float4 rows
     (900, 6, 64, 4, 17),      # the cap falls inside the first batch of nodes
