@@ -594,10 +594,11 @@ __global__ void __launch_bounds__(256) open_kernel(const float *base, int dim, b
                                                    const int32_t *count, int32_t *assign,
                                                    int32_t *changed)
 {
-    const int total = 4 * *count;
+    const int64_t total = 4 * (int64_t)*count;     // more than 2^31 from 2^29 points on
     const int sub = threadIdx.x & 3;
     // every lane of a group of four takes part in the exchange below
-    for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < total; e += gridDim.x * blockDim.x) {
+    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total;
+         e += (int64_t)gridDim.x * blockDim.x) {
         const OpenPoint &o = open[e >> 2];
         int c = o.c[sub];
         double v = __longlong_as_double(0x7ff0000000000000ll);

@@ -177,6 +177,22 @@ def test_select_hubs_equal_centroids(m):
         assert (hub.cpu().numpy() == ref["hub_ids"]).all()
 
 
+def test_select_hubs_more_open_points_than_a_quarter_of_int32():
+    # every centroid twice: all of 2^29 + 77 points are open (four lanes each
+    # decide them) and join the first of the two, as without the copies
+    n, places = 2 ** 29 + 77, 16
+    say("case: select_hubs, %d open points" % n)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(4)
+    base = torch.randint(0, 256, (n, 4), generator=gen, device="cuda", dtype=torch.float32)
+    init = torch.arange(places, dtype=torch.int32, device="cuda") * 1000
+    twice = torch.cat([init, init + 1])
+    base[twice[places:].long()] = base[init.long()]
+    _, _, one, _ = _ann().ann_select_hubs(base, places, 1, init)
+    _, _, two, _ = _ann().ann_select_hubs(base, 2 * places, 1, twice)
+    assert torch.equal(one, two)
+
+
 @pytest.mark.parametrize("n,dim,R,h,wcap", [
     (900, 6, 64, 3, 1),       # the hub alone; rows that are no float4 rows
     (900, 6, 64, 4, 17),      # the cap falls inside the first batch of nodes
