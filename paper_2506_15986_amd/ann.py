@@ -163,9 +163,28 @@ def workspace_size(op: str, n: int, dim: int, p0: int = 0, p1: int = 0) -> int:
     return int(_lib.ann_workspace_size(OP[op], n, dim, p0, p1))
 
 
-def workspace(op: str, n: int, dim: int, p0: int = 0, p1: int = 0, device=None) -> torch.Tensor:
-    nb = max(256, workspace_size(op, n, dim, p0, p1))
-    return torch.empty(nb, dtype=torch.uint8, device=device or "cuda")
+def _scratch(nbytes: int, device, stream=None) -> torch.Tensor:
+    """Scratch of a call that returns before its work is done: a block of the
+    stream the work is queued on, so that the allocator hands it out again in
+    that stream's order only."""
+    nbytes = max(256, int(nbytes))
+    if stream is None or torch.device(device).type != "cuda":
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    with torch.cuda.stream(stream):
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+
+
+def _filled_on(stream, *outs):
+    """Outputs of the current stream that the queued work on `stream` fills:
+    one that the caller drops is not handed out again before that."""
+    if stream is not None:
+        for t in outs:
+            if t is not None and t.is_cuda:
+                t.record_stream(stream)
+
+
+def workspace(op: str, n: int, dim: int, p0: int = 0, p1: int = 0, device=None, stream=None) -> torch.Tensor:
+    return _scratch(workspace_size(op, n, dim, p0, p1), device or "cuda", stream)
 
 
 def default_plan(n: int, dim: int, R: int, L_max: int) -> ann_search_plan:
@@ -212,7 +231,7 @@ def ann_search(base: torch.Tensor, graph: torch.Tensor, queries: torch.Tensor,
         ids, dist, stats = out
     trace = torch.empty((nq, trace_cap), dtype=torch.int32, device=dev) if trace_cap else None
     if ws is None:
-        ws = workspace("search", n, dim, nq, 0, device=dev)
+        ws = workspace("search", n, dim, nq, 0, device=dev, stream=stream)
     _check(_lib.ann_search(_ptr(base), n, dim, _ptr(graph), R, _ptr(queries), nq,
                            _ptr(entry_ids), int(medoid), _ptr(k), _ptr(L), k_max, _ptr(ids),
                            _ptr(dist), _ptr(stats), _ptr(trace), int(trace_cap),
@@ -530,7 +549,7 @@ def ann_hub_features(base, graph, medoid: int, hub_ids, assign, centroids, h: in
     dev = base.device
     f = torch.empty((nh, 32), dtype=torch.float32, device=dev)
     wsz = torch.empty((nh, 6), dtype=torch.int32, device=dev)
-    ws = workspace("hub_features", n, dim, nh, R, device=dev)
+    ws = workspace("hub_features", n, dim, nh, R, device=dev, stream=stream)
     _check(_lib.ann_hub_features(_ptr(base), n, dim, _ptr(graph), R, int(medoid), _ptr(hub_ids),
                                  nh, _ptr(assign), _ptr(centroids), h, wcap, int(standardise),
                                  _ptr(f), _ptr(wsz), _ptr(ws), ws.numel(), _stream(stream)))
@@ -549,12 +568,12 @@ def ann_make_labels(base, graph, queries, truth, hits: int, cand_hubs, hub_ids, 
     labels = torch.empty(nq, dtype=torch.int32, device=dev)
     table = torch.empty((nq, M), dtype=torch.int32, device=dev) if want_table else None
     flags = torch.empty(nq, dtype=torch.int32, device=dev)
-    nb = max(256, int(_lib.ann_labels_workspace_size(nq, M, kt)))
-    ws = torch.empty(nb, dtype=torch.uint8, device=dev)
+    ws = _scratch(_lib.ann_labels_workspace_size(nq, M, kt), dev, stream)
     _check(_lib.ann_make_labels(_ptr(base), n, dim, _ptr(graph), graph.shape[1], _ptr(queries),
                                 nq, _ptr(truth), kt, hits, _ptr(cand_hubs), M, _ptr(hub_ids),
                                 lad, len(L_ladder), _ptr(labels), _ptr(table), _ptr(flags),
                                 _ptr(ws), ws.numel(), _stream(stream)))
+    _filled_on(stream, labels, table, flags)
     return labels, table, flags
 
 
@@ -604,7 +623,7 @@ class Tower:
         st = self.struct()
         out = torch.empty((rows, self.dout), dtype=torch.float32, device=x.device)
         nb = max(256, int(_lib.ann_tower_workspace_size(ctypes.byref(st), rows)))
-        ws = torch.empty(nb, dtype=torch.uint8, device=x.device)
+        ws = _scratch(nb, x.device, stream)
         _check(_lib.ann_tower_forward(ctypes.byref(st), _ptr(x), rows, _ptr(out), _ptr(ws), nb,
                                       _stream(stream)))
         return out
@@ -624,7 +643,7 @@ def ann_train_step(qt: Tower, ht: Tower, train_q, batch_idx, labels, hub_in, tau
     qa, ha = qt.adam_struct(), ht.adam_struct()
     nb = int(_lib.ann_train_workspace_size(B, nh, qt.din, ht.din, qt.hidden, qt.dout))
     if ws is None or ws.numel() < nb:
-        ws = torch.empty(max(nb, 256), dtype=torch.uint8, device=dev)
+        ws = _scratch(nb, dev, stream)
     loss = torch.empty(1, dtype=torch.float32, device=dev)
     qe = torch.empty((B, qt.dout), dtype=torch.float32, device=dev) if want_emb else None
     he = torch.empty((nh, ht.dout), dtype=torch.float32, device=dev) if want_emb else None
@@ -663,7 +682,7 @@ def ann_train_step_hub(qt: Tower, ht: Tower, train_q, q_idx, hub_idx, P: int, N:
     qa, ha = qt.adam_struct(), ht.adam_struct()
     nb = ann_train_hub_workspace_size(Bh, P, N, qt.din, ht.din, qt.hidden, qt.dout)
     if ws is None or ws.numel() < nb:
-        ws = torch.empty(max(nb, 256), dtype=torch.uint8, device=dev)
+        ws = _scratch(nb, dev, stream)
     loss = torch.empty(1, dtype=torch.float32, device=dev)
     qe = torch.empty((rows, qt.dout), dtype=torch.float32, device=dev) if want_emb else None
     he = torch.empty((Bh, ht.dout), dtype=torch.float32, device=dev) if want_emb else None
@@ -804,7 +823,7 @@ class Fusion:
         nh, S = U.shape[0], U.shape[1]
         st = self.struct()
         nb = max(256, int(_lib.ann_fusion_workspace_size(ctypes.byref(st), nh)))
-        ws = torch.empty(nb, dtype=torch.uint8, device=p.device)
+        ws = _scratch(nb, p.device, stream)
         _check(_lib.ann_fusion_backward(ctypes.byref(st), _ptr(p), _ptr(U), _ptr(mask), nh, S,
                                         _ptr(dF), *[_ptr(t) for t in self.g], _ptr(ws), nb,
                                         _stream(stream)))

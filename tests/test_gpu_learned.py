@@ -740,6 +740,39 @@ def test_training_step_of_more_rows_than_a_launch_dimension_holds():
         assert float((a - b).norm()) <= 1e-2 * float(a.norm())
 
 
+def test_labels_scratch_of_another_stream():
+    # the call returns while its work still waits on its own stream; memory
+    # taken from the current stream meanwhile must not be its scratch or its
+    # outputs
+    ann = _ann()
+    ix = int_index()
+    base, g = _dev(ix["base"]), _dev(ix["graph"])
+    r = np.random.default_rng(8)
+    nq, M = 500, 8
+    q = _dev(r.integers(0, 256, size=(nq, ix["base"].shape[1])).astype(np.float32))
+    hubs = _dev(r.integers(0, ix["base"].shape[0], size=64).astype(np.int32))
+    cand = _dev(np.stack([r.permutation(64)[:M] for _ in range(nq)]).astype(np.int32))
+    truth = ann.ann_gt_knn(base, q, 10)[0]
+    ref = ann.ann_make_labels(base, g, q, truth, 9, cand, hubs, [10, 16, 32])
+    torch.cuda.synchronize()
+    say("case: labels on another stream")
+    st = torch.cuda.Stream()
+    nb = ann.ann_labels_workspace_size(nq, M, 10)
+    with torch.cuda.stream(st):
+        torch.cuda._sleep(20_000_000)         # some 10 ms
+    lab, tab, flags = ann.ann_make_labels(base, g, q, truth, 9, cand, hubs, [10, 16, 32], stream=st)
+    other = [torch.zeros(s, dtype=torch.uint8, device="cuda")
+             for s in (nb, nq * 4, nq * 4, nq * M * 4) for _ in range(4)]
+    mine = lambda t: range(t.data_ptr(), t.data_ptr() + t.numel() * t.element_size())
+    kept = [mine(t) for t in (lab, tab, flags)]
+    for t in other:
+        assert all(mine(t).stop <= k.start or k.stop <= mine(t).start for k in kept)
+    torch.cuda.synchronize()
+    assert all(not bool(t.any()) for t in other)
+    for a, b in zip((lab, tab, flags), ref):
+        assert torch.equal(a, b)
+
+
 @pytest.mark.parametrize("case", ["tables", "chunks"])
 def test_labels_row_lists(case):
     ann = _ann()
