@@ -158,52 +158,52 @@ struct FStage {
     }
 };
 
-// two products in one launch: blockIdx.z picks
-__global__ void __launch_bounds__(256) gemm_f32_kernel(GemmF g0, GemmF g1)
+// two products in one launch: blockIdx.z picks (`two` is 1 then, else 0); a
+// launch holds 65,535 workgroups in y, further rows follow in z
+__global__ void __launch_bounds__(256) gemm_f32_kernel(GemmF g0, GemmF g1, int two)
 {
-    const GemmF &g = blockIdx.z ? g1 : g0;
+    const GemmF &g = blockIdx.z & two ? g1 : g0;
+    const int64_t row = (int64_t)((blockIdx.z >> two) * gridDim.y + blockIdx.y) * FM;
     const int n0 = (int)blockIdx.x * FN;
-    if (n0 >= g.N) return;
+    if (row >= g.M || n0 >= g.N) return;
+    const int m0 = (int)row;
     __shared__ __align__(16) float As[FM * FS], Bs[FN * FS];
     const int t = threadIdx.x, lane = t & 63;
     const int w = __builtin_amdgcn_readfirstlane(t >> 6);
-    for (int64_t row = (int64_t)blockIdx.y * FM; row < g.M; row += (int64_t)gridDim.y * FM) {
-        const int m0 = (int)row;
-        FStage<FM> a;
-        FStage<FN> b;
-        a.load(g.A, g.sam, g.sak, m0, g.M, 0, g.K);
-        b.load(g.B, g.sbn, g.sbk, n0, g.N, 0, g.K);
-        float acc[FR] = {};
-        for (int k0 = 0; k0 < g.K; k0 += FK) {
-            __syncthreads();
-            a.store(As, g.sak);
-            b.store(Bs, g.sbk);
-            __syncthreads();
-            if (k0 + FK < g.K) {
-                a.load(g.A, g.sam, g.sak, m0, g.M, k0 + FK, g.K);
-                b.load(g.B, g.sbn, g.sbk, n0, g.N, k0 + FK, g.K);
-            }
-#pragma unroll
-            for (int k = 0; k < FK; k += 4) {
-                const float4 y = *reinterpret_cast<const float4 *>(Bs + lane * FS + k);
-                float4 x[FR];
-#pragma unroll
-                for (int r = 0; r < FR; ++r)
-                    x[r] = *reinterpret_cast<const float4 *>(As + (FR * w + r) * FS + k);
-#pragma unroll
-                for (int r = 0; r < FR; ++r) {
-                    acc[r] += x[r].x * y.x;
-                    acc[r] += x[r].y * y.y;
-                    acc[r] += x[r].z * y.z;
-                    acc[r] += x[r].w * y.w;
-                }
-            }
+    FStage<FM> a;
+    FStage<FN> b;
+    a.load(g.A, g.sam, g.sak, m0, g.M, 0, g.K);
+    b.load(g.B, g.sbn, g.sbk, n0, g.N, 0, g.K);
+    float acc[FR] = {};
+    for (int k0 = 0; k0 < g.K; k0 += FK) {
+        __syncthreads();
+        a.store(As, g.sak);
+        b.store(Bs, g.sbk);
+        __syncthreads();
+        if (k0 + FK < g.K) {
+            a.load(g.A, g.sam, g.sak, m0, g.M, k0 + FK, g.K);
+            b.load(g.B, g.sbn, g.sbk, n0, g.N, k0 + FK, g.K);
         }
 #pragma unroll
-        for (int r = 0; r < FR; ++r) {
-            const int m = m0 + FR * w + r;
-            if (m < g.M && n0 + lane < g.N) g.C[(int64_t)m * g.ldc + n0 + lane] = g.alpha * acc[r];
+        for (int k = 0; k < FK; k += 4) {
+            const float4 y = *reinterpret_cast<const float4 *>(Bs + lane * FS + k);
+            float4 x[FR];
+#pragma unroll
+            for (int r = 0; r < FR; ++r)
+                x[r] = *reinterpret_cast<const float4 *>(As + (FR * w + r) * FS + k);
+#pragma unroll
+            for (int r = 0; r < FR; ++r) {
+                acc[r] += x[r].x * y.x;
+                acc[r] += x[r].y * y.y;
+                acc[r] += x[r].z * y.z;
+                acc[r] += x[r].w * y.w;
+            }
         }
+    }
+#pragma unroll
+    for (int r = 0; r < FR; ++r) {
+        const int m = m0 + FR * w + r;
+        if (m < g.M && n0 + lane < g.N) g.C[(int64_t)m * g.ldc + n0 + lane] = g.alpha * acc[r];
     }
 }
 
@@ -764,11 +764,10 @@ ann_status gemm_f32(const GemmF &g, const GemmF *h, hipStream_t st)
 {
     const GemmF &g1 = h ? *h : g;
     const int M = g.M > g1.M ? g.M : g1.M, N = g.N > g1.N ? g.N : g1.N;
-    // at most 65,535 workgroups in y: more rows take turns
-    const int64_t my = ((int64_t)M + FM - 1) / FM;
-    hipLaunchKernelGGL(gemm_f32_kernel,
-                       dim3((unsigned)((N + FN - 1) / FN), (unsigned)(my < 65535 ? my : 65535), h ? 2 : 1),
-                       dim3(256), 0, st, g, g1);
+    const unsigned my = ((unsigned)M + FM - 1) / FM, two = h ? 1u : 0u;
+    const unsigned ny = my < 65535u ? my : 65535u;
+    hipLaunchKernelGGL(gemm_f32_kernel, dim3((unsigned)((N + FN - 1) / FN), ny, ((my + ny - 1) / ny) << two),
+                       dim3(256), 0, st, g, g1, (int)two);
     ANN_LAUNCHED();
     return ANN_OK;
 }
