@@ -74,7 +74,13 @@ enum {
  *   MAKE_LABELS   n, dim, p0 = nq,        p1 = M (candidates per query)
  *   HUB_FEATURES  n, dim, p0 = n_hubs,    p1 = R
  * Returns 0 for an unknown op.  The tower, training and entry-selection
- * calls have their own size functions below. */
+ * calls have their own size functions below.
+ * GT_KNN, BUILD_GRAPH and the size functions of the partitioned build, the
+ * group candidates and the navigation graph return what real-valued data
+ * needs (an FP16 copy of the base rows among it).  Integer data needs less,
+ * and the calls accept that: as much as n x dim bytes for each side and the
+ * rows' lists.  Real-valued data then goes through the plain FP64 engine, with
+ * the same results but slower. */
 size_t ann_workspace_size(int32_t op, int64_t n, int32_t dim, int32_t p0, int32_t p1);
 
 /* ------------------------------------------------------------------------ */

@@ -62,6 +62,8 @@ size_t navgraph_ws(int nh, int e, int s)
     return knn_workspace(nh, nh, e, s) + medoid_ws(nh, e) + 512;
 }
 
+size_t navgraph_accepts(int nh, int e, int s) { return knn_accepts(nh, nh, e, s) + medoid_ws(nh, e) + 512; }
+
 size_t entry_select_ws(int nq, const ann_tower *w)
 {
     size_t b = round_up((size_t)nq * w->dout * 4, 256);       // query embeddings
@@ -87,12 +89,12 @@ extern "C" ann_status ann_navgraph_build(const float *hub_emb, int32_t n_hubs, i
     ANN_REQUIRE(hub_emb && hub_graph && hub_entry && workspace, "a required pointer is NULL");
     ANN_REQUIRE(n_hubs >= 2 && dim >= 1 && dim <= 1024, "bad n_hubs or dim");
     ANN_REQUIRE(s >= 1 && s < n_hubs, "s must be in [1, n_hubs)");
-    ANN_REQUIRE(ws_bytes >= navgraph_ws(n_hubs, dim, s), "workspace too small");
+    ANN_REQUIRE(ws_bytes >= navgraph_accepts(n_hubs, dim, s), "workspace too small");
     hipStream_t st = static_cast<hipStream_t>(stream);
     Carve cv{static_cast<unsigned char *>(workspace)};
-    const size_t kws = knn_workspace(n_hubs, n_hubs, dim, s);
-    void *kbuf = cv.take<unsigned char>(kws);
     void *mbuf = cv.take<unsigned char>(medoid_ws(n_hubs, dim));
+    void *kbuf = cv.p;
+    const size_t kws = ws_bytes - (size_t)(cv.p - static_cast<unsigned char *>(workspace));
     ann_status r = knn_run(hub_emb, n_hubs, dim, hub_emb, n_hubs, s, true, hub_graph, nullptr,
                            nullptr, kbuf, kws, st, 2);
     if (r != ANN_OK) return r;

@@ -864,20 +864,34 @@ __global__ void scatter_cand_kernel(const int32_t *loc_ids, const double *loc_d2
 
 }  // namespace
 
+// cand ids, d2 and the steps after them
+static size_t build_rest(int64_t n, int dim, int K, int R)
+{
+    return round_up((size_t)n * K * 4, 256) + round_up((size_t)n * K * 8, 256) + tail_ws(n, dim, R);
+}
+
 size_t build_graph_ws(int64_t n, int dim, int K, int R)
 {
-    size_t b = knn_workspace(n, n, dim, K);
-    b += round_up((size_t)n * K * 4, 256) + round_up((size_t)n * K * 8, 256);  // cand ids, d2
-    return b + tail_ws(n, dim, R);
+    return knn_workspace(n, n, dim, K) + build_rest(n, dim, K, R);
+}
+
+static size_t group_rest(int dim, int K, int64_t max_mem, int64_t max_home)
+{
+    size_t b = round_up((size_t)max_mem * dim * 4, 256) + round_up((size_t)max_home * dim * 4, 256);
+    b += round_up((size_t)max_mem * 4, 256) + round_up((size_t)max_home * 4, 256) * 2;
+    b += round_up((size_t)max_home * K * 4, 256) + round_up((size_t)max_home * K * 8, 256);
+    return b + 1024;
 }
 
 size_t group_cand_ws(int dim, int K, int64_t max_mem, int64_t max_home)
 {
-    size_t b = knn_workspace(max_mem, max_home, dim, K);
-    b += round_up((size_t)max_mem * dim * 4, 256) + round_up((size_t)max_home * dim * 4, 256);
-    b += round_up((size_t)max_mem * 4, 256) + round_up((size_t)max_home * 4, 256) * 2;
-    b += round_up((size_t)max_home * K * 4, 256) + round_up((size_t)max_home * K * 8, 256);
-    return b + 1024;
+    return knn_workspace(max_mem, max_home, dim, K) + group_rest(dim, K, max_mem, max_home);
+}
+
+// what the call is accepted with (knn_accepts)
+static size_t group_cand_accepts(int dim, int K, int64_t max_mem, int64_t max_home)
+{
+    return knn_accepts(max_mem, max_home, dim, K) + group_rest(dim, K, max_mem, max_home);
 }
 
 }  // namespace ann
@@ -898,16 +912,15 @@ extern "C" ann_status ann_build_graph(const float *base, int64_t n, int32_t dim,
     ANN_REQUIRE(knn_k <= n - 1, "knn_k must be < n");
     ANN_REQUIRE(alpha >= 1.0f, "alpha must be >= 1");
     ANN_REQUIRE(aligned(base, 16), "base must be 16-byte aligned");
-    ANN_REQUIRE(ws_bytes >= ann_workspace_size(ANN_OP_BUILD_GRAPH, n, dim, knn_k, R),
-                "workspace too small");
-    hipStream_t st = static_cast<hipStream_t>(stream);
     const int K = knn_k;
+    ANN_REQUIRE(ws_bytes >= knn_accepts(n, n, dim, K) + build_rest(n, dim, K, R), "workspace too small");
+    hipStream_t st = static_cast<hipStream_t>(stream);
     Carve cv{static_cast<unsigned char *>(workspace)};
-    size_t kws = knn_workspace(n, n, dim, K);
-    void *knn_ws = cv.take<unsigned char>(kws);
     int32_t *cand = cv.take<int32_t>((size_t)n * K);
     double *cd2 = cv.take<double>((size_t)n * K);
     TailBufs t = take_tail(cv, n, dim);
+    void *knn_ws = cv.p;
+    const size_t kws = ws_bytes - (size_t)(cv.p - static_cast<unsigned char *>(workspace));
     // exact kNN candidates (self excluded), then pruning, medoid, repair
     ann_status s = knn_run(base, n, dim, base, n, K, true, cand, nullptr, cd2, knn_ws, kws, st, 0);
     if (s != ANN_OK) return s;
@@ -968,12 +981,11 @@ ann_status group_lists(const int32_t *groups_dev, int64_t n, int32_t n_member, i
     return ANN_OK;
 }
 
-// candidate lists of the home points of groups [g0, g1)
+// candidate lists of the home points of groups [g0, g1); `bytes` of memory at cv
 ann_status group_candidates(const float *base, int dim, int K, const GroupLists &L, int g0, int g1,
-                            int32_t *cand, double *cd2, Carve &cv, hipStream_t st)
+                            int32_t *cand, double *cd2, Carve cv, size_t bytes, hipStream_t st)
 {
-    const size_t kws = knn_workspace(L.max_mem, L.max_home, dim, K);
-    void *knn_ws = cv.take<unsigned char>(kws);
+    const unsigned char *begin = cv.p;
     float *mrows = cv.take<float>((size_t)L.max_mem * dim);
     float *hrows = cv.take<float>((size_t)L.max_home * dim);
     int32_t *mem_d = cv.take<int32_t>((size_t)L.max_mem);
@@ -981,6 +993,8 @@ ann_status group_candidates(const float *base, int dim, int K, const GroupLists 
     int32_t *self_d = cv.take<int32_t>((size_t)L.max_home);
     int32_t *loc_ids = cv.take<int32_t>((size_t)L.max_home * K);
     double *loc_d2 = cv.take<double>((size_t)L.max_home * K);
+    void *knn_ws = cv.p;
+    const size_t kws = bytes - (size_t)(cv.p - begin);
     std::vector<int32_t> selfc((size_t)L.max_home);
     for (int g = g0; g < g1; ++g) {
         const int64_t m = L.ms[(size_t)g + 1] - L.ms[(size_t)g];
@@ -1049,11 +1063,11 @@ extern "C" ann_status ann_group_candidates(const float *base, int64_t n, int32_t
     GroupLists L;
     ann_status s = group_lists(groups, n, n_member, n_groups, st, L);
     if (s != ANN_OK) return s;
-    ANN_REQUIRE(ws_bytes >= group_cand_ws(dim, knn_k, L.max_mem, L.max_home),
+    ANN_REQUIRE(ws_bytes >= group_cand_accepts(dim, knn_k, L.max_mem, L.max_home),
                 "workspace too small (largest member set %lld, largest home set %lld)",
                 (long long)L.max_mem, (long long)L.max_home);
     Carve cv{static_cast<unsigned char *>(workspace)};
-    return group_candidates(base, dim, knn_k, L, g_begin, g_end, cand, cand_d2, cv, st);
+    return group_candidates(base, dim, knn_k, L, g_begin, g_end, cand, cand_d2, cv, ws_bytes, st);
 }
 
 extern "C" size_t ann_graph_from_candidates_workspace_size(int64_t n, int32_t dim, int32_t R)
@@ -1111,18 +1125,19 @@ extern "C" ann_status ann_build_graph_partitioned(const float *base, int64_t n, 
     GroupLists L;
     ann_status s = group_lists(groups, n, n_member, n_groups, st, L);
     if (s != ANN_OK) return s;
-    ANN_REQUIRE(ws_bytes >= ann_build_graph_partitioned_workspace_size(n, dim, knn_k, R, L.max_mem,
-                                                                        L.max_home),
+    const size_t lists = round_up((size_t)n * knn_k * 4, 256) + round_up((size_t)n * knn_k * 8, 256);
+    ANN_REQUIRE(ws_bytes >= lists + std::max(tail_ws(n, dim, R),
+                                             group_cand_accepts(dim, knn_k, L.max_mem, L.max_home)),
                 "workspace too small (largest member set %lld, largest home set %lld)",
                 (long long)L.max_mem, (long long)L.max_home);
     const int K = knn_k;
     Carve cv{static_cast<unsigned char *>(workspace)};
     int32_t *cand = cv.take<int32_t>((size_t)n * K);
     double *cd2 = cv.take<double>((size_t)n * K);
-    Carve rest = cv;     // the kNN staging and the tail's buffers share what is left
-    s = group_candidates(base, dim, K, L, 0, n_groups, cand, cd2, cv, st);
+    // the kNN staging and the tail's buffers share what is left
+    s = group_candidates(base, dim, K, L, 0, n_groups, cand, cd2, cv, ws_bytes - lists, st);
     if (s != ANN_OK) return s;
-    TailBufs t = take_tail(rest, n, dim);
+    TailBufs t = take_tail(cv, n, dim);
     return graph_tail(base, n, dim, cand, cd2, K, R, alpha, graph, medoid, bridges, t, st);
 }
 

@@ -26,12 +26,17 @@ struct KnnArgs {
     double *out_d;
 };
 
-// Workspace bytes for knn_run.
+// Workspace bytes for knn_run on any data, and the (smaller) bytes that a call
+// is accepted with: integer data needs no more, and real-valued data then goes
+// through the plain FP64 engine, or its shortlist in smaller batches of rows.
 size_t knn_workspace(int64_t n, int64_t rows, int dim, int K);
+size_t knn_accepts(int64_t n, int64_t rows, int dim, int K);
 
 // Exact top-K by (squared L2, id) of `rows` query rows against `base`.
 // force_engine: 0 = pick (int8 matrix cores when all values are integers in
-// [0,255] and dim % 32 == 0, else FP64), 1 = int8 only, 2 = FP64 only.
+// [0,255] and dim % 32 == 0, else the real-valued engines: the FP16 shortlist
+// with FP64 distances, the plain FP64 engine for what that leaves), 1 = int8
+// only, 2 = the real-valued engines only.
 // With exclude_self, query row g never returns base column self_col[g]
 // (column g when self_col is null).  Synchronises `st`.
 ann_status knn_run(const float *base, int64_t n, int dim, const float *queries, int64_t rows,

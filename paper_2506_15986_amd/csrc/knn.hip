@@ -884,7 +884,8 @@ struct Plan {
     int64_t slice_len;
 };
 
-Plan plan(int64_t n, int64_t rows, int K, bool one_slice)
+// most: slices at most (0: no limit)
+Plan plan(int64_t n, int64_t rows, int K, int64_t most)
 {
     Plan p{};
     if (n < 1) n = 1;      // a plan for empty inputs too, as f16::plan
@@ -900,7 +901,8 @@ Plan plan(int64_t n, int64_t rows, int K, bool one_slice)
     const int64_t by_merge = kMaxMerged / p.Kp > 1 ? kMaxMerged / p.Kp : 1;
     if (s > by_len) s = by_len;
     if (s > by_merge) s = by_merge;
-    if (s < 1 || one_slice) s = 1;
+    if (most > 0 && s > most) s = most;
+    if (s < 1) s = 1;
     p.slice_len = ((n + s - 1) / s + kCols - 1) / kCols * kCols;
     p.slices = (int)((n + p.slice_len - 1) / p.slice_len);
     if (p.slices < 1) p.slices = 1;
@@ -918,15 +920,13 @@ size_t cluster_ws(int64_t n, int dim)
            round_up((size_t)blocks * 4, 256);
 }
 
-size_t workspace(int64_t n, int64_t rows, int dim, int K)
+size_t workspace(const Plan &p, int64_t n, int64_t rows, int dim, bool clustered)
 {
-    // the caller's queries may or may not be the base rows: room for both orders
-    const Plan p = plan(n, rows, K, false);
     size_t b = round_up((size_t)rows * p.slices * p.cap * 8, 256);
     b += round_up((size_t)rows * p.slices * 4, 256);
     b += round_up((size_t)n * dim, 256) + round_up((size_t)n * 4, 256);
     b += round_up((size_t)rows * dim, 256) + round_up((size_t)rows * 4, 256);
-    if (cluster_order(n, rows)) b += cluster_ws(n, dim);
+    if (clustered) b += cluster_ws(n, dim);
     return b + 256;
 }
 
@@ -959,13 +959,52 @@ static size_t f64_buffer(int64_t rows, int K)
     return round_up((size_t)rows * knn_cap(K) * sizeof(Ent), 256);
 }
 
+// what the int8 engine and the plain FP64 engine take
+size_t knn_accepts(int64_t n, int64_t rows, int dim, int K)
+{
+    const size_t f64 = f64_buffer(rows, K) + 256;
+    // the caller's queries may or may not be the base rows: room for both orders
+    size_t i8b = i8::workspace(i8::plan(n, rows, K, 0), n, rows, dim, false);
+    if (i8::cluster_order(n, rows)) {
+        const size_t c = i8::workspace(i8::plan(n, rows, K, 1), n, rows, dim, true);
+        i8b = c > i8b ? c : i8b;
+    }
+    return (f64 > i8b ? f64 : i8b) + 256;
+}
+
+// memory of the FP16 shortlist's lists over batches of `rows` rows; the plain
+// engine takes rows that are left in batches of what fits
+static size_t real_lists(int64_t n, int64_t rows, int K)
+{
+    const size_t h = f16::list_bytes(n, rows, K, device_cus());
+    const size_t f = f64_buffer(rows < knn::kRows ? rows : knn::kRows, K);
+    return h > f ? h : f;
+}
+
+static size_t real_bytes(int64_t n, int64_t rows, int64_t batch, int dim, int K)
+{
+    return f16::operand_bytes(n, rows, dim) + f16::row_bytes(batch, dim) + real_lists(n, batch, K) + 256;
+}
+
 size_t knn_workspace(int64_t n, int64_t rows, int dim, int K)
 {
-    const size_t f64 = f64_buffer(rows, K);
-    const size_t i8b = i8::workspace(n, rows, dim, K);
-    const size_t f16b = f16::buffer_bytes(n, rows, K, device_cus());
-    const size_t real = (f64 > f16b ? f64 : f16b) + f16::operand_bytes(n, rows, dim) + 256;
-    return (real > i8b ? real : i8b) + 256;
+    const size_t least = knn_accepts(n, rows, dim, K);
+    if (n < 1 || rows < 1) return least;
+    const int64_t batches = (rows + f16::kBatchRows - 1) / f16::kBatchRows;
+    const size_t real = real_bytes(n, rows, f16::batch_rows(rows, batches), dim, K) + 256;
+    return real > least ? real : least;
+}
+
+// rows of a batch of the FP16 shortlist in `bytes` of memory, as few batches as
+// that allows; 0: too little, the plain engine's turn
+static int64_t real_batch(int64_t n, int64_t rows, int dim, int K, size_t bytes)
+{
+    if (dim > (1 << 20)) return 0;   // a workgroup's 256 rows stay below 2 GiB (buffer offsets)
+    for (int64_t batches = (rows + f16::kMostRows - 1) / f16::kMostRows;; ++batches) {
+        const int64_t b = f16::batch_rows(rows, batches);
+        if (real_bytes(n, rows, b, dim, K) <= bytes) return b;
+        if (b <= f16::kLeastRows) return 0;
+    }
 }
 
 ann_status data_is_uint8(const float *x, int64_t count, int *flag_dev, bool *result, hipStream_t st)
@@ -1001,27 +1040,29 @@ __global__ void set_words_kernel(uint32_t *p, int count)
     if ((int)threadIdx.x < count) p[threadIdx.x] = 0u;
 }
 
-// Real-valued data: the FP16 shortlist, its second level for the rows it
-// leaves, the plain engine for what that leaves.  Synchronises.
-ann_status run_f16(KnnArgs f, int *flag, unsigned char *p, hipStream_t st)
+// Real-valued data: the FP16 shortlist in batches of `batch` rows, its second
+// level for the rows it leaves, the plain engine for what that leaves.
+// Synchronises.
+ann_status run_f16(KnnArgs f, int64_t batch, int *flag, unsigned char *p, hipStream_t st)
 {
     const int64_t n = f.n, rows = f.rows;
     const int dim = f.dim, dp = f16::padded(dim), cus = device_cus();
     uint32_t *bits = reinterpret_cast<uint32_t *>(flag) + 1;
     int32_t *todo_n = reinterpret_cast<int32_t *>(flag) + 2;      // one count per level
     Carve cv{p};
-    const size_t fb = f64_buffer(rows, f.K), hb = f16::buffer_bytes(n, rows, f.K, cus);
-    unsigned char *buffers = cv.take<unsigned char>(fb > hb ? fb : hb);
-    _Float16 *bh = cv.take<_Float16>((size_t)n * dp), *bl = cv.take<_Float16>((size_t)n * dp);
-    _Float16 *qh = cv.take<_Float16>((size_t)rows * dp), *ql = cv.take<_Float16>((size_t)rows * dp);
+    const size_t lists = real_lists(n, batch, f.K);
+    unsigned char *buffers = cv.take<unsigned char>(lists);
+    _Float16 *bh = cv.take<_Float16>((size_t)n * dp);
     float *bV = cv.take<float>((size_t)n), *bE = cv.take<float>((size_t)n);
-    float *qV = cv.take<float>((size_t)rows), *qE = cv.take<float>((size_t)rows);
     float *centre = cv.take<float>((size_t)dim);
-    float *first = cv.take<float>((size_t)rows);
     _Float16 *sh = cv.take<_Float16>((size_t)f16::kMaxSample * dp);
     _Float16 *sl = cv.take<_Float16>((size_t)f16::kMaxSample * dp);
     float *sV = cv.take<float>((size_t)f16::kMaxSample), *sE = cv.take<float>((size_t)f16::kMaxSample);
     int32_t *todo[2] = {cv.take<int32_t>((size_t)rows), cv.take<int32_t>((size_t)rows)};
+    // a batch's rows
+    _Float16 *qh = cv.take<_Float16>((size_t)batch * dp), *ql = cv.take<_Float16>((size_t)batch * dp);
+    float *qV = cv.take<float>((size_t)batch), *qE = cv.take<float>((size_t)batch);
+    float *first = cv.take<float>((size_t)batch);
     hipLaunchKernelGGL(set_words_kernel, dim3(1), dim3(64), 0, st, bits, 3);
     ANN_LAUNCHED();
     hipLaunchKernelGGL(f16::centre_kernel, dim3((unsigned)((dim + 63) / 64)), dim3(1024), 0, st, f.base,
@@ -1039,29 +1080,31 @@ ann_status run_f16(KnnArgs f, int *flag, unsigned char *p, hipStream_t st)
         spread(f.queries, rows);
         ANN_LAUNCHED();
     }
-    const bool grouped = same && f.self_col == nullptr && n >= f16::kGroupedMinN;
+    const bool grouped = same && f.self_col == nullptr && n >= f16::kGroupedMinN && n <= f16::kGroupedMaxN;
+    const bool vec4 = dim % 4 == 0 && aligned(f.base, 16) && aligned(f.queries, 16);
     int32_t *perm = nullptr;       // the rows in group order
-    int32_t left = (int32_t)rows;
+    int64_t left = rows;
     for (int level = 0; level < 2 && left > 0; ++level) {
         // level 0 takes every row, level 1 the rows listed in todo[0]
         const f16::Coef co = f16::coef(dim, level == 1);
-        const int32_t *list = level ? todo[0] : nullptr;
         const bool shared = same && level == 0;
-        auto convert = [&](const float *x, int64_t m, const int32_t *which, _Float16 *h, _Float16 *l,
-                           float *V, float *E) {
-            const dim3 grid((unsigned)((m + 3) / 4));
+        auto convert = [&](const float *x, int64_t m, const int32_t *which, int64_t of, _Float16 *h,
+                           _Float16 *l, float *V, float *E) {
+            const int64_t b = (m + 3) / 4;
+            const dim3 grid((unsigned)(b < (1 << 22) ? b : 1 << 22));
             if (level)
                 hipLaunchKernelGGL(f16::convert_kernel<true>, grid, dim3(256), 0, st, x, m, dim, dp,
-                                   centre, bits, which, co, h, l, V, E);
+                                   centre, bits, which, of, co, h, l, V, E);
             else
                 hipLaunchKernelGGL(f16::convert_kernel<false>, grid, dim3(256), 0, st, x, m, dim, dp,
-                                   centre, bits, which, co, h, l, V, E);
+                                   centre, bits, which, of, co, h, l, V, E);
         };
         const int32_t *start_col = nullptr;
+        // the columns: FP16 rows at level 0 (in group order, when grouped),
+        // bounds alone at level 1
+        convert(f.base, n, nullptr, 0, level ? nullptr : bh, nullptr, bV, bE);
+        ANN_LAUNCHED();
         if (level == 0 && grouped) {
-            // level 0 leaves the second parts' arrays and the rows' norms free
-            convert(f.base, n, nullptr, bl, bl, qV, qE);
-            ANN_LAUNCHED();
             const int64_t blocks = (n + f16::kRowsWG - 1) / f16::kRowsWG;
             int32_t *group = cv.take<int32_t>((size_t)n);
             perm = cv.take<int32_t>((size_t)n);
@@ -1069,14 +1112,14 @@ ann_status run_f16(KnnArgs f, int *flag, unsigned char *p, hipStream_t st)
             int32_t *hist = cv.take<int32_t>((size_t)f16::kGroups + 1);
             int32_t *gstart = cv.take<int32_t>((size_t)f16::kGroups + 1);
             int32_t *scol = cv.take<int32_t>((size_t)blocks);
-            hipLaunchKernelGGL(f16::sample_kernel, dim3(f16::kGroups), dim3(64), 0, st, bl, qV, n,
+            hipLaunchKernelGGL(f16::sample_kernel, dim3(f16::kGroups), dim3(64), 0, st, bh, bV, n,
                                f16::groups_of(n), dp, sh, sV);
             ANN_LAUNCHED();
             hipLaunchKernelGGL(set_words_kernel, dim3(1), dim3(f16::kGroups), 0, st,
                                reinterpret_cast<uint32_t *>(hist), f16::kGroups);
             ANN_LAUNCHED();
             hipLaunchKernelGGL(f16::nearest_sample_kernel, dim3((unsigned)((n + 63) / 64)), dim3(256), 0,
-                               st, bl, n, dp, sh, sV, group, hist);
+                               st, bh, n, dp, sh, sV, group, hist);
             ANN_LAUNCHED();
             hipLaunchKernelGGL(i8::group_starts_kernel, dim3(1), dim3(64), 0, st, hist, f16::kGroups,
                                gstart, hist);
@@ -1084,98 +1127,116 @@ ann_status run_f16(KnnArgs f, int *flag, unsigned char *p, hipStream_t st)
             hipLaunchKernelGGL(i8::place_rows_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
                                group, n, hist, perm);
             ANN_LAUNCHED();
-            hipLaunchKernelGGL(f16::permute_kernel, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, st, bl, qV,
-                               qE, perm, n, dp, bh, bV, bE);
+            // the rows again, in group order (a second copy of the FP16 rows to
+            // permute from would take their memory twice)
+            convert(f.base, n, perm, 0, bh, nullptr, bV, bE);
             ANN_LAUNCHED();
             hipLaunchKernelGGL(f16::start_kernel, dim3((unsigned)((blocks + 255) / 256)), dim3(256), 0, st,
-                               group, perm, gstart, n, blocks, scol);
+                               group, perm, gstart, blocks, scol);
             ANN_LAUNCHED();
             start_col = scol;
-        } else {
-            convert(f.base, n, nullptr, bh, bl, bV, bE);
-            ANN_LAUNCHED();
         }
-        if (!shared) {
-            convert(f.queries, left, list, qh, ql, qV, qE);
-            ANN_LAUNCHED();
-        }
-        // fewer rows may take more slices, as long as their buffers fit
-        const f16::Plan all = f16::plan(n, rows, f.K, cus, 0, false);
-        const f16::Plan pl = level     ? f16::plan(n, left, f.K, cus, rows * all.slices / left, false)
-                             : grouped ? f16::plan(n, rows, f.K, cus, 0, true)
-                                       : all;
-        f16::Args a{};
-        a.bh = bh;
-        a.bl = bl;
-        a.qh = shared ? bh : qh;
-        a.ql = ql;
-        a.bV = bV;
-        a.bE = bE;
-        a.qV = shared ? bV : qV;
-        a.qE = shared ? bE : qE;
-        a.bits = bits;
-        a.n = n;
-        a.rows = left;
-        a.dpad = dp;
-        a.K = f.exclude_self ? pl.Kp : f.K;
-        a.keep = pl.keep;
-        a.slices = pl.slices;
-        a.slice_len = pl.slice_len;
-        a.start = start_col;
-        a.buf = reinterpret_cast<uint64_t *>(buffers);
-        a.cnt = reinterpret_cast<int32_t *>(buffers + round_up((size_t)left * pl.slices * pl.cap * 8, 256));
-        ann_status s = ANN_OK;
-        if (pl.S) {
-            float *est = reinterpret_cast<float *>(buffers);
-            s = level ? f16::first_thresholds<true>(a, pl.S, est, first, sh, sl, sV, sE, st)
-                      : f16::first_thresholds<false>(a, pl.S, est, first, sh, sl, sV, sE, st);
+        const f16::Plan all = f16::plan(n, batch, f.K, cus, 0, false);
+        int sampled = 0;
+        for (int64_t r0 = 0; r0 < left; r0 += batch) {
+            const int64_t m = left - r0 < batch ? left - r0 : batch;
+            const int32_t *list = level ? todo[0] + r0 : perm ? perm + r0 : nullptr;
+            if (!shared) {
+                convert(level ? f.queries : f.queries + r0 * dim, m, list, 0, qh, ql, qV, qE);
+                ANN_LAUNCHED();
+            }
+            // fewer rows may take more slices, as long as their lists fit
+            const f16::Plan pl = f16::plan(n, m, f.K, cus, batch * all.slices / m, level == 0 && grouped);
+            f16::Args a{};
+            a.bh = bh;
+            a.qh = shared ? bh + r0 * dp : qh;
+            a.ql = ql;
+            a.base = f.base;
+            a.c = centre;
+            a.dim = dim;
+            a.vec4 = vec4;
+            a.bV = bV;
+            a.bE = bE;
+            a.qV = shared ? bV + r0 : qV;
+            a.qE = shared ? bE + r0 : qE;
+            a.bits = bits;
+            a.n = n;
+            a.rows = m;
+            a.dpad = dp;
+            a.K = f.exclude_self ? pl.Kp : f.K;
+            a.keep = pl.keep;
+            a.slices = pl.slices;
+            a.slice_len = pl.slice_len;
+            a.start = start_col ? start_col + r0 / f16::kRowsWG : nullptr;
+            a.buf = reinterpret_cast<uint64_t *>(buffers);
+            a.cnt = reinterpret_cast<int32_t *>(buffers + round_up((size_t)m * pl.slices * pl.cap * 8, 256));
+            ann_status s = ANN_OK;
+            if (pl.S) {
+                if (!start_col && sampled != pl.S) {
+                    if (level)
+                        convert(f.base, pl.S, nullptr, n, sh, sl, sV, sE);
+                    else
+                        hipLaunchKernelGGL(f16::pick_columns_kernel, dim3(pl.S), dim3(64), 0, st, bh, bV,
+                                           bE, n, pl.S, dp, sh, sV, sE);
+                    ANN_LAUNCHED();
+                    sampled = pl.S;
+                }
+                float *est = reinterpret_cast<float *>(buffers);
+                s = level ? f16::first_thresholds<true>(a, pl.S, est, first, sh, sl, sV, sE, st)
+                          : f16::first_thresholds<false>(a, pl.S, est, first, sh, sl, sV, sE, st);
+                if (s != ANN_OK) return s;
+                a.first = first;
+            }
+            s = level ? f16::launch_tiles<true>(a, pl.cap, st) : f16::launch_tiles<false>(a, pl.cap, st);
             if (s != ANN_OK) return s;
-            a.first = first;
+            f16::FinalArgs fa{};
+            fa.base = f.base;
+            fa.queries = f.queries;
+            fa.rows = m;
+            fa.dim = dim;
+            fa.row0 = r0;
+            fa.row_list = list;
+            fa.col_id = level ? nullptr : perm;
+            fa.qE = a.qE;
+            fa.bE = bE;
+            fa.bits = bits;
+            fa.buf = a.buf;
+            fa.cnt = a.cnt;
+            fa.slices = pl.slices;
+            fa.cap = pl.cap;
+            fa.K = f.K;
+            fa.Kp = a.K;
+            fa.most = pl.most;
+            fa.sort = pl.sort;
+            fa.vec4 = vec4;
+            fa.exclude = f.exclude_self;
+            fa.self_col = f.self_col;
+            fa.out_ids = f.out_ids;
+            fa.out_f = f.out_f;
+            fa.out_d = f.out_d;
+            fa.todo = todo[level];
+            fa.todo_n = todo_n + level;
+            const size_t lds = f16::final_words(pl.most, pl.sort) + (size_t)pl.sort * 4;
+            ANN_HIP(hipFuncSetAttribute((const void *)f16::final_kernel,
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+            hipLaunchKernelGGL(f16::final_kernel, dim3((unsigned)m), dim3(64), lds, st, fa);
+            ANN_LAUNCHED();
         }
-        s = level ? f16::launch_tiles<true>(a, pl.cap, st) : f16::launch_tiles<false>(a, pl.cap, st);
-        if (s != ANN_OK) return s;
-        f16::FinalArgs fa{};
-        fa.base = f.base;
-        fa.queries = f.queries;
-        fa.rows = left;
-        fa.dim = dim;
-        fa.row_list = level ? list : perm;
-        fa.col_id = level ? nullptr : perm;
-        fa.qE = a.qE;
-        fa.bE = bE;
-        fa.bits = bits;
-        fa.buf = a.buf;
-        fa.cnt = a.cnt;
-        fa.slices = pl.slices;
-        fa.cap = pl.cap;
-        fa.K = f.K;
-        fa.Kp = a.K;
-        fa.most = pl.most;
-        fa.sort = pl.sort;
-        fa.vec4 = dim % 4 == 0 && aligned(f.base, 16) && aligned(f.queries, 16);
-        fa.exclude = f.exclude_self;
-        fa.self_col = f.self_col;
-        fa.out_ids = f.out_ids;
-        fa.out_f = f.out_f;
-        fa.out_d = f.out_d;
-        fa.todo = todo[level];
-        fa.todo_n = todo_n + level;
-        const size_t lds = f16::final_words(pl.most, pl.sort) + (size_t)pl.sort * 4;
-        ANN_HIP(hipFuncSetAttribute((const void *)f16::final_kernel,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-        hipLaunchKernelGGL(f16::final_kernel, dim3((unsigned)left), dim3(64), lds, st, fa);
-        ANN_LAUNCHED();
         uint32_t h[3];
         ANN_HIP(hipMemcpyAsync(h, bits, sizeof(h), hipMemcpyDeviceToHost, st));
         ANN_HIP(hipStreamSynchronize(st));
-        left = (int32_t)h[1 + level];
+        left = (int64_t)h[1 + level];
         f.row_list = todo[level];
         if (h[0] >= f16::kNotFinite) break;  // values that are not finite: the plain engine
     }
-    if (left > 0) {
-        f.rows = left;
-        f.buf = reinterpret_cast<Ent *>(buffers);
-        return run_f64(f, st);
+    // what is left, in batches whose lists fit
+    int64_t per = (int64_t)(lists / ((size_t)f.cap * sizeof(Ent)));
+    if (per > knn::kRows) per = per / knn::kRows * knn::kRows;
+    f.buf = reinterpret_cast<Ent *>(buffers);
+    for (int64_t r0 = 0; r0 < left; r0 += per, f.row_list += per) {
+        f.rows = left - r0 < per ? left - r0 : per;
+        ann_status s = run_f64(f, st);
+        if (s != ANN_OK) return s;
     }
     return ANN_OK;
 }
@@ -1189,8 +1250,10 @@ ann_status knn_run(const float *base, int64_t n, int dim, const float *queries, 
                    void *ws, size_t ws_bytes, hipStream_t st, int force_engine,
                    const int32_t *self_col)
 {
-    ANN_REQUIRE(ws_bytes >= knn_workspace(n, rows, dim, K), "kNN workspace too small");
     if (rows == 0) return ANN_OK;
+    // one slice of the int8 engine, the plain engine
+    const size_t least = i8::workspace(i8::plan(n, rows, K, 1), n, rows, dim, false) + 256;
+    ANN_REQUIRE(ws_bytes >= least && ws_bytes >= f64_buffer(rows, K) + 256, "kNN workspace too small");
     unsigned char *p = static_cast<unsigned char *>(ws);
     int *flag = reinterpret_cast<int *>(p);
     p += 256;
@@ -1207,9 +1270,15 @@ ann_status knn_run(const float *base, int64_t n, int dim, const float *queries, 
     }
     if (force_engine == 1 && !use_int) return fail(ANN_EINVAL, "int8 engine needs integer data in [0,255]");
     if (use_int) {
-        const bool clustered = queries == base && self_col == nullptr &&
-                               i8::cluster_order(n, rows) && n <= 0x7FFFFFFF;
-        const i8::Plan pl = i8::plan(n, rows, K, clustered);
+        // as many slices as the memory holds (a size is asked for the largest
+        // of several calls, and fewer rows may want more slices)
+        const size_t room = ws_bytes - 256;
+        i8::Plan pl = i8::plan(n, rows, K, 1);
+        const bool clustered = queries == base && self_col == nullptr && i8::cluster_order(n, rows) &&
+                               n <= 0x7FFFFFFF && i8::workspace(pl, n, rows, dim, true) <= room;
+        if (!clustered) pl = i8::plan(n, rows, K, 0);
+        while (pl.slices > 1 && i8::workspace(pl, n, rows, dim, clustered) > room)
+            pl = i8::plan(n, rows, K, pl.slices - 1);
         i8::Args a{};
         a.buf = reinterpret_cast<uint64_t *>(p);
         p += round_up((size_t)rows * pl.slices * pl.cap * 8, 256);
@@ -1341,8 +1410,8 @@ ann_status knn_run(const float *base, int64_t n, int dim, const float *queries, 
         a.out_f = out_f;
         a.out_d = out_d;
         a.cap = (int)knn_cap(K);
-        // a workgroup's 256 rows stay below 2 GiB (buffer offsets)
-        ann_status s = dim <= (1 << 20) ? run_f16(a, flag, p, st) : run_f64(a, st);
+        const int64_t batch = real_batch(n, rows, dim, K, ws_bytes - 256);
+        ann_status s = batch ? run_f16(a, batch, flag, p, st) : run_f64(a, st);
         if (s != ANN_OK) return s;
     }
     ANN_HIP(hipStreamSynchronize(st));
@@ -1364,7 +1433,7 @@ extern "C" ann_status ann_gt_knn(const float *base, int64_t n, int32_t dim, cons
     ANN_REQUIRE(k >= 1 && k <= 1024, "k must be in [1, 1024]");
     ANN_REQUIRE(nq >= 0, "nq must be >= 0");
     ANN_REQUIRE(!exclude_self || nq <= n, "exclude_self needs nq <= n");
-    ANN_REQUIRE(ws_bytes >= ann_workspace_size(ANN_OP_GT_KNN, n, dim, nq, k), "workspace too small");
+    ANN_REQUIRE(ws_bytes >= knn_accepts(n, nq, dim, k), "workspace too small");
     if (nq == 0) return ANN_OK;
     return knn_run(base, n, dim, queries, nq, k, exclude_self != 0, out_ids, out_dist, nullptr,
                    workspace, ws_bytes, static_cast<hipStream_t>(stream), 0);

@@ -127,40 +127,39 @@ __device__ inline float scale_of(uint32_t bits)
     return __uint_as_float((uint32_t)(k + 127) << 23);
 }
 
-// one wavefront per row: h (and l, for the listed rows of the second level),
-// V and E.  rows: NULL = all n rows, else `n` row numbers.
+// One wavefront per row: h (and l, for the second level), V and E.  Row i of
+// the result is row rows[i], or with `of` > 0 the i-th of n evenly spaced rows
+// among `of`, or row i.  hi NULL: V and E alone.
 template <bool LO>
 __global__ void __launch_bounds__(256) convert_kernel(const float *x, int64_t n, int dim, int dpad,
                                                       const float *c, const uint32_t *bits,
-                                                      const int32_t *rows, Coef co, _Float16 *hi,
-                                                      _Float16 *lo, float *V, float *E)
+                                                      const int32_t *rows, int64_t of, Coef co,
+                                                      _Float16 *hi, _Float16 *lo, float *V, float *E)
 {
-    const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (i >= n) return;
-    const int64_t r = rows ? rows[i] : i;
     const int lane = threadIdx.x & 63;
     const float s = scale_of(*bits);
-    double v = 0.0;
-    for (int j = lane; j < dpad; j += 64) {
-        float y = 0.f;
-        if (j < dim) {
-            const float xv = x[r * dim + j], cv = c[j];
-            const double d = ((double)xv - (double)cv) * (double)s;
-            v += d * d;
-            y = (xv - cv) * s;
-        }
-        const _Float16 h = (_Float16)y;
-        if (!LO) hi[i * dpad + j] = h;
-        else {
+    for (int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); i < n; i += (int64_t)gridDim.x * 4) {
+        const int64_t r = rows ? (int64_t)rows[i] : of ? i * of / n : i;
+        double v = 0.0;
+        for (int j = lane; j < dpad; j += 64) {
+            float y = 0.f;
+            if (j < dim) {
+                const float xv = x[r * dim + j], cv = c[j];
+                const double d = ((double)xv - (double)cv) * (double)s;
+                v += d * d;
+                y = (xv - cv) * s;
+            }
+            if (!hi) continue;
+            const _Float16 h = (_Float16)y;
             hi[i * dpad + j] = h;
-            lo[i * dpad + j] = (_Float16)(y - (float)h);
+            if (LO) lo[i * dpad + j] = (_Float16)(y - (float)h);
         }
-    }
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    if (lane == 0) {
-        const float vf = (float)v;
-        V[i] = vf;
-        E[i] = co.eV * vf + co.eS * sqrtf(vf) + co.e0;
+        for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+        if (lane == 0) {
+            const float vf = (float)v;
+            V[i] = vf;
+            E[i] = co.eV * vf + co.eS * sqrtf(vf) + co.e0;
+        }
     }
 }
 
@@ -170,6 +169,7 @@ __global__ void __launch_bounds__(256) convert_kernel(const float *x, int64_t n,
 // columns and visiting them first.  Only the visiting order changes.
 constexpr int kGroups = 256;
 constexpr int64_t kGroupedMinN = 16384;
+constexpr int64_t kGroupedMaxN = 1 << 28;    // of a launch with a wavefront per 16 rows
 
 inline int groups_of(int64_t n)
 {
@@ -245,35 +245,20 @@ __global__ void __launch_bounds__(256) nearest_sample_kernel(const _Float16 *h, 
     }
 }
 
-// rows in group order
-__global__ void __launch_bounds__(256) permute_kernel(const _Float16 *h, const float *V, const float *E,
-                                                      const int32_t *perm, int64_t n, int dpad,
-                                                      _Float16 *ph, float *pV, float *pE)
-{
-    const int64_t p = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (p >= n) return;
-    const int lane = threadIdx.x & 63;
-    const int64_t r = perm[p];
-    for (int j = 8 * lane; j < dpad; j += 512)
-        *reinterpret_cast<v8h *>(ph + p * dpad + j) = *reinterpret_cast<const v8h *>(h + r * dpad + j);
-    if (lane == 0) {
-        pV[p] = V[r];
-        pE[p] = E[r];
-    }
-}
-
 // each workgroup's first column: the start of the group of its first row
-__global__ void start_kernel(const int32_t *group, const int32_t *perm, const int32_t *start, int64_t n,
+__global__ void start_kernel(const int32_t *group, const int32_t *perm, const int32_t *start,
                              int64_t blocks, int32_t *start_col)
 {
     const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (b < blocks) start_col[b] = start[group[perm[b * kRowsWG]]];
-    (void)n;
 }
 
 struct Args {
-    const _Float16 *bh, *bl;   // columns, n x dpad
+    const _Float16 *bh, *bl;   // columns, n x dpad (second level: of the estimates only)
     const _Float16 *qh, *ql;   // rows, rows x dpad
+    const float *base, *c;     // second level: the columns' vectors, split as they are staged
+    int dim;
+    int vec4;                  // ... whole, aligned groups of four floats
     const float *bV, *bE, *qV, *qE;
     const uint32_t *bits;      // the data's spread
     int64_t n, rows;
@@ -396,21 +381,16 @@ __global__ void __launch_bounds__(256) threshold_kernel(const float *est, int64_
     if (lane == 0) first[g] = unord(T[0]) + 2.f * qE[g];
 }
 
-// the sample columns of a pass without groups: S evenly spaced columns
-__global__ void __launch_bounds__(64) pick_columns_kernel(const _Float16 *h, const _Float16 *l,
-                                                          const float *V, const float *E, int64_t n,
-                                                          int S, int dpad, _Float16 *oh, _Float16 *ol,
+// the sample columns of a first-level pass without groups: S evenly spaced ones
+__global__ void __launch_bounds__(64) pick_columns_kernel(const _Float16 *h, const float *V, const float *E,
+                                                          int64_t n, int S, int dpad, _Float16 *oh,
                                                           float *oV, float *oE)
 {
     const int s = blockIdx.x;
     const int64_t c = (int64_t)s * n / S;
-    for (int j = 8 * (int)threadIdx.x; j < dpad; j += 512) {
+    for (int j = 8 * (int)threadIdx.x; j < dpad; j += 512)
         *reinterpret_cast<v8h *>(oh + (size_t)s * dpad + j) =
             *reinterpret_cast<const v8h *>(h + c * dpad + j);
-        if (ol)
-            *reinterpret_cast<v8h *>(ol + (size_t)s * dpad + j) =
-                *reinterpret_cast<const v8h *>(l + c * dpad + j);
-    }
     if (threadIdx.x == 0) {
         oV[s] = V[c];
         oE[s] = E[c];
@@ -447,6 +427,10 @@ constexpr size_t tile_lds()
 // row that takes no columns, past the last or given up, is NaN: no value
 // passes it, an infinite one neither.
 //
+// The second level's columns come from the vectors themselves and are split
+// into h and l on the way to LDS (as many bytes as the two halves would have;
+// few rows get here, and the halves of all columns were most of the memory).
+//
 // Measured against the plain FP64 engine, whole calls: ann_build_graph of
 // 50,001 x 96 (K = 64) 113.5 -> 8.0 ms, of which this kernel 109 -> 2.6 ms; the
 // 10 nearest of 1,000 queries among 150,000 x 960 526 -> 1.3 ms (this kernel
@@ -459,6 +443,7 @@ tile_kernel(Args a)
     constexpr int CAP = 64 * CAPW;
     if (*a.bits >= kNotFinite) return;
     constexpr int RB = CAPW <= 4 ? 4 : CAPW <= 8 ? 2 : 1;         // rows cut together
+    constexpr bool SPLIT = LO && !EST;
     constexpr int AS = kRowsWG * 8 / 256, BS = kCols * 8 / 256;   // 16-byte slots per thread
     extern __shared__ __align__(16) unsigned char dyn[];
     v8h *Ah = reinterpret_cast<v8h *>(dyn);
@@ -506,6 +491,7 @@ tile_kernel(Args a)
         r_cnt[t] = 0;
     }
     typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+    const float scale = SPLIT ? scale_of(*a.bits) : 0.f;
     v4u sa[AS], sb[BS], la[LO ? AS : 1], lb[LO ? BS : 1];
     float s_low = 0.f;
     // Thread t stages 16-byte slot t % 8 of rows t / 8 + 32 e.  Buffer loads
@@ -539,8 +525,27 @@ tile_kernel(Args a)
         }
 #pragma unroll
         for (int e = 0; e < BS; ++e) {
-            sb[e] = __builtin_amdgcn_raw_buffer_load_b128(rbh, vo + 32 * e * rowb, 128 * ch, 0);
-            if (LO) lb[e] = __builtin_amdgcn_raw_buffer_load_b128(rbl, vo + 32 * e * rowb, 128 * ch, 0);
+            if constexpr (SPLIT) {
+                // eight floats of a column: sb the first four, lb the others
+                const int64_t c = c0 + (t >> 3) + 32 * e;
+                const int j = kDk * ch + 8 * (t & 7);
+                const float *src = a.base + c * a.dim + j;
+                sb[e] = lb[e] = v4u{0u, 0u, 0u, 0u};
+                if (c >= a.n) continue;
+                if (a.vec4) {
+                    if (j < a.dim) sb[e] = *reinterpret_cast<const v4u *>(src);
+                    if (j + 4 < a.dim) lb[e] = *reinterpret_cast<const v4u *>(src + 4);
+                } else {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        if (j + q < a.dim) sb[e][q] = __float_as_uint(src[q]);
+                        if (j + 4 + q < a.dim) lb[e][q] = __float_as_uint(src[4 + q]);
+                    }
+                }
+            } else {
+                sb[e] = __builtin_amdgcn_raw_buffer_load_b128(rbh, vo + 32 * e * rowb, 128 * ch, 0);
+                if (LO) lb[e] = __builtin_amdgcn_raw_buffer_load_b128(rbl, vo + 32 * e * rowb, 128 * ch, 0);
+            }
         }
         if (ch == 0 && t < kCols) {
             const int64_t c = c0 + t;
@@ -559,10 +564,32 @@ tile_kernel(Args a)
             Ah[st_at + 256 * e] = __builtin_bit_cast(v8h, sa[e]);
             if (LO) Al[st_at + 256 * e] = __builtin_bit_cast(v8h, la[e]);
         }
+        float cv[8];
+        if constexpr (SPLIT) {
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const int j = kDk * ch + 8 * (t & 7) + q;
+                cv[q] = j < a.dim ? a.c[j] : 0.f;
+            }
+        }
 #pragma unroll
         for (int e = 0; e < BS; ++e) {
-            Bh[st_at + 256 * e] = __builtin_bit_cast(v8h, sb[e]);
-            if (LO) Bl[st_at + 256 * e] = __builtin_bit_cast(v8h, lb[e]);
+            if constexpr (SPLIT) {
+                // convert_kernel's h and l; zero past the row's end
+                v8h hi, lo;
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    const float x = __uint_as_float(q < 4 ? sb[e][q & 3] : lb[e][q & 3]);
+                    const float y = kDk * ch + 8 * (t & 7) + q < a.dim ? (x - cv[q]) * scale : 0.f;
+                    hi[q] = (_Float16)y;
+                    lo[q] = (_Float16)(y - (float)hi[q]);
+                }
+                Bh[st_at + 256 * e] = hi;
+                Bl[st_at + 256 * e] = lo;
+            } else {
+                Bh[st_at + 256 * e] = __builtin_bit_cast(v8h, sb[e]);
+                if (LO) Bl[st_at + 256 * e] = __builtin_bit_cast(v8h, lb[e]);
+            }
         }
         if (ch == 0 && t < kCols) c_low[t] = s_low;
     };
@@ -755,7 +782,8 @@ struct FinalArgs {
     const float *base, *queries;
     int64_t rows;
     int dim;
-    const int32_t *row_list;   // query row of list row g (NULL: g)
+    int64_t row0;
+    const int32_t *row_list;   // query row of list row g (NULL: row0 + g)
     const int32_t *col_id;     // base row of column p (NULL: p)
     const float *qE, *bE;
     const uint32_t *bits;      // the data's spread (level 1: not finite = every row goes on)
@@ -803,7 +831,7 @@ __global__ void __launch_bounds__(64) final_kernel(FinalArgs a)
     int32_t *pick = reinterpret_cast<int32_t *>(dyn + final_words(a.most, a.sort));   // `sort`
     const int lane = threadIdx.x;
     const int64_t g = blockIdx.x;
-    const int64_t q = a.row_list ? a.row_list[g] : g;
+    const int64_t q = a.row_list ? (int64_t)a.row_list[g] : a.row0 + g;
     // the slices' counts, one per lane, and their places; then the words,
     // sixteen lanes to a slice, four slices' loads in flight
     const int mine = lane < a.slices ? a.cnt[g * a.slices + lane] : 0;
@@ -971,27 +999,45 @@ inline Plan plan(int64_t n, int64_t rows, int K, int cus, int64_t max_slices, bo
 
 inline int padded(int dim) { return (dim + 31) / 32 * 32; }
 
-// bytes besides the row buffers
+// Memory of a pass: the columns' operands, and what a batch of rows takes.  The
+// rows go through in batches of equal size, so that the lists (4 KB a row at
+// K = 64) stay bounded: a size asks for batches of up to kBatchRows, a call
+// takes as few batches as the memory it has allows.
+constexpr int64_t kBatchRows = 1 << 18;    // 1,024 workgroups
+constexpr int64_t kLeastRows = 1 << 14;    // no batches smaller than this
+constexpr int64_t kMostRows = 1 << 24;     // of a launch with a wavefront per row
+
+inline int64_t batch_rows(int64_t rows, int64_t batches)
+{
+    const int64_t b = (int64_t)round_up((size_t)((rows + batches - 1) / batches), kRowsWG);
+    return b < rows ? b : rows;
+}
+
 inline size_t operand_bytes(int64_t n, int64_t rows, int dim)
 {
     const size_t dp = (size_t)padded(dim);
-    size_t b = round_up((size_t)n * dp * 2, 256) * 2 + round_up((size_t)rows * dp * 2, 256) * 2;
-    b += round_up((size_t)n * 4, 256) * 2 + round_up((size_t)rows * 4, 256) * 2;
-    b += round_up((size_t)dim * 4, 256) + round_up((size_t)rows * 4, 256) * 3;
+    size_t b = round_up((size_t)n * dp * 2, 256) + round_up((size_t)n * 4, 256) * 2;
+    b += round_up((size_t)dim * 4, 256) + round_up((size_t)rows * 4, 256) * 2;
     b += round_up((size_t)kMaxSample * dp * 2, 256) * 2 + round_up((size_t)kMaxSample * 4, 256) * 2;
     if (rows == n) {             // the cluster order
-        b += round_up((size_t)n * 4, 256) * 2 + round_up((size_t)kGroups * dp * 2, 256);
-        b += round_up((size_t)(kGroups + 1) * 4, 256) * 3;
+        b += round_up((size_t)n * 4, 256) * 2;
+        b += round_up((size_t)(kGroups + 1) * 4, 256) * 2;
         b += round_up((size_t)((n + kRowsWG - 1) / kRowsWG) * 4, 256);
     }
     return b;
 }
 
-inline size_t buffer_bytes(int64_t n, int64_t rows, int K, int cus)
+inline size_t list_bytes(int64_t n, int64_t rows, int K, int cus)
 {
     const Plan p = plan(n, rows, K, cus, 0, false);
     return round_up((size_t)rows * p.slices * p.cap * 8, 256) +
            round_up((size_t)rows * p.slices * 4, 256);
+}
+
+// besides the lists
+inline size_t row_bytes(int64_t rows, int dim)
+{
+    return round_up((size_t)rows * padded(dim) * 2, 256) * 2 + round_up((size_t)rows * 4, 256) * 3;
 }
 
 template <int CAPW, bool LO>
@@ -1018,15 +1064,12 @@ ann_status launch_tiles(const Args &a, int cap, hipStream_t st)
 }
 
 // the rows' first thresholds from S columns of `a`: its own group's, or the
-// sample copied to (sh, sl, sV, sE)
+// sample (sh, sl, sV, sE)
 template <bool LO>
-ann_status first_thresholds(Args a, int S, float *est, float *first, _Float16 *sh, _Float16 *sl,
-                            float *sV, float *sE, hipStream_t st)
+ann_status first_thresholds(Args a, int S, float *est, float *first, const _Float16 *sh,
+                            const _Float16 *sl, const float *sV, const float *sE, hipStream_t st)
 {
     if (!a.start) {
-        hipLaunchKernelGGL(pick_columns_kernel, dim3(S), dim3(64), 0, st, a.bh, a.bl, a.bV, a.bE, a.n, S,
-                           a.dpad, sh, LO ? sl : nullptr, sV, sE);
-        ANN_LAUNCHED();
         a.bh = sh;
         a.bl = sl;
         a.bV = sV;

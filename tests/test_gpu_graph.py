@@ -287,6 +287,148 @@ def test_knn_of_values_beyond_fp16_products_matches_oracle(n, d, k, kind):
         assert (dist.cpu().numpy() == ref_d2.astype(np.float32)).all()
 
 
+@pytest.mark.parametrize("n,nq,d,k,kind", [
+    (5_000, 600, 49, 128, "tight"),        # the second level's columns: odd rows,
+    (3_000, 300, 130, 12, "flat"),         # ... two and a half stages of dimensions,
+    (70_000, 3, 97, 50, "tight"),          # ... several column slices
+])
+def test_real_valued_second_level_matches_oracle(n, nq, d, k, kind):
+    test_real_valued_knn_matches_oracle(n, nq, d, k, kind)
+
+
+@pytest.mark.parametrize("exclude", [False, True])
+@pytest.mark.parametrize("n,d,k,kind", [(16_385, 20, 30, "normal"), (16_384, 33, 16, "tight"),
+                                        (20_011, 36, 20, "copies"), (20_011, 100, 64, "tight")])
+def test_real_valued_all_pairs_in_group_order(n, d, k, kind, exclude):
+    # from 16,384 rows on, all pairs go through in the order of their groups
+    base, _ = _real_points(kind, n, 1, d)
+    say("case: real-valued all pairs in group order n=%d d=%d k=%d %s" % (n, d, k, kind))
+    x = _dev(base)
+    ids, dist = _ann().ann_gt_knn(x, x, k, exclude_self=exclude)
+    torch.cuda.synchronize()
+    ids, dist = ids.cpu().numpy(), dist.cpu().numpy()
+    rows = np.unique(np.concatenate([np.arange(0, n, max(1, n // 300)), [n - 1]]))
+    ref_ids, ref_d2 = oracle.knn(base, base[rows], k + 1)
+    for t, row in enumerate(rows):
+        keep = [j for j in range(k + 1) if not exclude or ref_ids[t, j] != row][:k]
+        assert (ids[row] == ref_ids[t, keep]).all(), row
+        assert (dist[row] == ref_d2[t, keep].astype(np.float32)).all(), row
+
+
+def test_real_valued_knn_in_batches_of_rows():
+    # more query rows than go through at a time (2^18): half of them have
+    # neighbours, the others equal more columns than a list holds and pass
+    # both levels on to the FP64 engine, more of them than a batch too
+    n, nq, d, k = 2_000, 600_001, 21, 8
+    base, q = _real_points("copies", n, 300, d)
+    r = np.random.default_rng(2)
+    pick = np.where(r.random(nq) < 0.5, 0, r.integers(1, 300, nq))
+    say("case: real-valued kNN in batches of rows")
+    ids, dist = _ann().ann_gt_knn(_dev(base), _dev(q)[_dev(pick)].contiguous(), k)
+    torch.cuda.synchronize()
+    ref_ids, ref_d2 = oracle.knn(base, q, k)
+    assert (q[0] == base).all(1).sum() > 512 and (pick == 0).sum() > 2 ** 18
+    assert (ids.cpu().numpy() == ref_ids[pick]).all()
+    assert (dist.cpu().numpy() == ref_d2.astype(np.float32)[pick]).all()
+
+
+def test_real_valued_all_pairs_in_batches_of_rows():
+    n, d, k = 300_001, 12, 10
+    base, _ = _real_points("normal", n, 1, d)
+    say("case: real-valued all pairs in batches of rows")
+    x = _dev(base)
+    ids, dist = _ann().ann_gt_knn(x, x, k)
+    torch.cuda.synchronize()
+    rows = np.concatenate([np.arange(0, n, 3_001), [n - 1]])
+    ref_ids, ref_d2 = oracle.knn(base, base[rows], k)
+    assert (ids.cpu().numpy()[rows] == ref_ids).all()
+    assert (dist.cpu().numpy()[rows] == ref_d2.astype(np.float32)).all()
+
+
+def test_real_valued_knn_of_more_rows_than_a_launch_of_wavefronts():
+    # 2^26 rows of one wavefront each are 2^32 threads
+    n, d, k = 2 ** 26 + 1_001, 4, 5
+    say("case: real-valued kNN among %d rows" % n)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(1)
+    base = torch.randn((n, d), generator=gen, device="cuda")
+    q = torch.cat([torch.randn((2, d), generator=gen, device="cuda"), base[-1:] + 1e-3])
+    ids, dist = _ann().ann_gt_knn(base, q, k)
+    for t in range(3):
+        d2 = ((base.double() - q[t].double()) ** 2).sum(1)
+        v, i = torch.topk(d2, k, largest=False)
+        assert torch.equal(ids[t].long(), i)
+        # one rounding to FP32, after FP64 sums in another order
+        assert torch.allclose(dist[t].double(), v, rtol=2.0 ** -23, atol=0)
+
+
+def _start_size(n, rows, dim, k):
+    """The bytes that a kNN call took when it held the int8 and the FP64 engine alone."""
+    ru = lambda x: (x + 255) // 256 * 256
+    c = 2
+    while c < k + 64:
+        c *= 2
+    kp, cap = k + 1, 64
+    while cap < kp + 64 or (cap < 512 and cap < 2 * kp + 64):
+        cap *= 2
+    blocks = (rows + 255) // 256
+    s = max(1, min(-(-2048 // blocks), max(n // 4096, 1), max(4096 // kp, 1)))
+    sl = (-(-n // s) + 63) // 64 * 64
+    slices = -(-n // sl)
+    b = ru(rows * slices * cap * 8) + ru(rows * slices * 4) + ru(n * dim) + ru(n * 4) + ru(rows * dim) + ru(rows * 4)
+    if rows == n and n >= 65536:
+        b += 2 * ru(n * 4) + ru(256 * dim) + 3 * ru(257 * 4) + ru((n + 255) // 256 * 4)
+    return max(ru(rows * c * 16) + 256, b + 256) + 256
+
+
+@pytest.mark.parametrize("n,nq,d,k,ints", [
+    (9_000, 700, 96, 10, False), (50_000, 50_000, 32, 16, True), (50_000, 50_000, 32, 16, False),
+    (70_000, 70_000, 64, 64, True), (150_000, 5, 260, 10, False), (400, 3, 9, 1024, False),
+])
+def test_knn_takes_the_smaller_workspace(n, nq, d, k, ints):
+    # a buffer for the int8 and the FP64 engine alone is enough for either
+    # data, less is refused, and the results are the same
+    ann = _ann()
+    r = np.random.default_rng(n)
+    x = r.integers(0, 256, size=(n, d)) if ints else np.rint(r.normal(size=(n, d)) * 2 ** 10) / 2 ** 10
+    base = _dev(x.astype(np.float32))
+    q = base if nq == n else base[torch.randperm(n, device="cuda")[:nq]] + 0.25
+    ref = ann.ann_gt_knn(base, q, k)
+    nb = _start_size(n, nq, d, k)
+    say("case: kNN in the smaller workspace n=%d nq=%d d=%d k=%d" % (n, nq, d, k))
+    ids, dist = torch.empty_like(ref[0]), torch.empty_like(ref[1])
+    buf = torch.full((nb + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+    call = lambda size: ann._lib.ann_gt_knn(ann._ptr(base), n, d, ann._ptr(q), nq, k, 0, ann._ptr(ids),
+                                            ann._ptr(dist), ann._ptr(buf), size, ann._stream())
+    assert call(nb) == ann.ANN_OK
+    torch.cuda.synchronize()
+    assert torch.equal(ids, ref[0]) and torch.equal(dist, ref[1])
+    assert bool((buf[nb:] == 0x5A).all())
+    if nq < n:      # all pairs in group order take a little less
+        assert call(nb - 1) == ann.ANN_EINVAL
+
+
+@pytest.mark.parametrize("ints,d", [(True, 32), (False, 20)])
+def test_group_candidates_of_a_smaller_group_with_more_slices(ints, d):
+    # 65,000 rows go through in more column slices than 70,000: the workspace,
+    # sized for the larger group, serves both
+    ann = _ann()
+    n, first, K = 135_000, 70_000, 8
+    r = np.random.default_rng(d)
+    x = r.integers(0, 256, size=(n, d)) if ints else np.rint(r.normal(size=(n, d)) * 2 ** 10) / 2 ** 10
+    base = _dev(x.astype(np.float32))
+    lab = (torch.arange(n, device="cuda") >= first).to(torch.int32)[:, None].contiguous()
+    cand = torch.empty((n, K), dtype=torch.int32, device="cuda")
+    cd2 = torch.empty((n, K), dtype=torch.float64, device="cuda")
+    say("case: candidates of two groups, d=%d" % d)
+    ann.ann_group_candidates(base, K, lab, 2, 0, 2, cand, cd2)
+    for a, b in ((0, first), (first, n)):
+        part = base[a:b].contiguous()
+        ids, dist = ann.ann_gt_knn(part, part, K, exclude_self=True)
+        assert torch.equal(cand[a:b], ids + a)
+        assert torch.equal(cd2[a:b].float(), dist)
+
+
 def _repair_points(which):
     r = np.random.default_rng(17)
     if which == "equal points":
