@@ -990,21 +990,24 @@ size_t knn_workspace(int64_t n, int64_t rows, int dim, int K)
 {
     const size_t least = knn_accepts(n, rows, dim, K);
     if (n < 1 || rows < 1) return least;
-    const int64_t batches = (rows + f16::kBatchRows - 1) / f16::kBatchRows;
-    const size_t real = real_bytes(n, rows, f16::batch_rows(rows, batches), dim, K) + 256;
+    const size_t real = real_bytes(n, rows, rows < f16::kBatchRows ? rows : f16::kBatchRows, dim, K) + 256;
     return real > least ? real : least;
 }
 
-// rows of a batch of the FP16 shortlist in `bytes` of memory, as few batches as
-// that allows; 0: too little, the plain engine's turn
+// rows of a batch of the FP16 shortlist in `bytes` of memory; 0: too little, the
+// plain engine's turn
 static int64_t real_batch(int64_t n, int64_t rows, int dim, int K, size_t bytes)
 {
     if (dim > (1 << 20)) return 0;   // a workgroup's 256 rows stay below 2 GiB (buffer offsets)
-    for (int64_t batches = (rows + f16::kMostRows - 1) / f16::kMostRows;; ++batches) {
-        const int64_t b = f16::batch_rows(rows, batches);
-        if (real_bytes(n, rows, b, dim, K) <= bytes) return b;
-        if (b <= f16::kLeastRows) return 0;
-    }
+    auto fits = [&](int64_t b) { return real_bytes(n, rows, b, dim, K) <= bytes; };
+    if (rows <= f16::kMostRows && fits(rows)) return rows;
+    const int64_t round = 2 * (int64_t)device_cus() * f16::kRowsWG;
+    int64_t b = rows < f16::kMostRows ? rows : f16::kMostRows;
+    for (b = b / round * round; b >= round; b -= round)
+        if (fits(b)) return b;
+    for (b = round / 2 / f16::kRowsWG * f16::kRowsWG; b >= f16::kLeastRows; b = b / 2 / f16::kRowsWG * f16::kRowsWG)
+        if (b < rows && fits(b)) return b;
+    return 0;
 }
 
 ann_status data_is_uint8(const float *x, int64_t count, int *flag_dev, bool *result, hipStream_t st)
