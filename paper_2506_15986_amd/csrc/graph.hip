@@ -264,7 +264,11 @@ __global__ void argmin_final_kernel(const DKey *partial, int count, DKey *out)
 //            m(u) = u, and w is reached by the search from m(w), so "v is
 //            reached when u's turn comes" reads m(v) < u.  m is the fixpoint
 //            of m(w) = min m(v) over edges v -> w, shortened by m(w) =
-//            min(m(w), m(m(w))) (what reaches m(w) reaches w).
+//            min(m(w), m(m(w))) (what reaches m(w) reaches w).  Where distances
+//            in the graph are long (points along a line) that would still take
+//            a sweep per edge of the way; then the labels of the other
+//            direction are kept too, and nodes found to lie on a common cycle
+//            are joined: they share both labels.
 //  matching  Every u takes the first v of its list with m(v) < u whose slot
 //            no smaller u took.  All nodes prefer the smaller u, so this is
 //            the one stable matching, and proposals in any order reach it:
@@ -276,17 +280,21 @@ __global__ void argmin_final_kernel(const DKey *partial, int count, DKey *out)
 // The reverse repair has the same form along reversed edges, without the
 // competition for slots (the link leaves w itself).
 //
-// Bound: the FP64 distances of the scans; the labels take eight sweeps over
-// the graph rows per phase.  Measured at 300,000 x 128, R = 32 (518 scans):
-// labels 0.65 ms, lists under 0.1 ms, scans 12 ms in 4 passes; one workgroup
-// that followed the definition bridge by bridge, with a host round trip and a
-// pass over the base per scan, took 566 ms.  The whole build 739 -> 159 ms,
-// and 191 -> 114 ms on 50,001 x 96 unit vectors (76 ms of repair before).
+// Bound: the FP64 distances of the scans.  The labels take about eight sweeps
+// over the graph rows per phase where distances in the graph are short, and
+// about as many again as joining takes rounds where they are long; only a chain
+// of one-way edges still takes a sweep per edge.  Measured at 300,000 x 128,
+// R = 32 (518 scans): labels 0.65 ms, lists under 0.1 ms, scans 2.2 ms in 4
+// passes; one workgroup that followed the definition bridge by bridge, with a
+// host round trip and a pass over the base per scan, took 566 ms.  From the
+// candidate lists of 100,000 points on a line, R = 16: 1.6 ms with their ids in
+// order, 9.9 ms shuffled (838 and 357 ms without joining).
 constexpr int32_t kFree = 0x7fffffff;   // a slot nobody holds
 constexpr int SCAN_U = 8;               // u's that share one load of a base row
 constexpr int SCAN_BATCH = 512;         // u's per scan launch
 constexpr int SCAN_BLOCKS = 256;        // workgroups per group of SCAN_U u's
 constexpr int SCAN_DK = 128;            // dimensions staged in LDS at a time
+constexpr int LONG_SWEEPS = 16;         // sweeps after which joining starts
 
 // atomics are performed in L2; read what they write the same way
 __device__ inline int32_t ld_agent(const int32_t *p)
@@ -296,6 +304,7 @@ __device__ inline int32_t ld_agent(const int32_t *p)
 
 struct RepairCounts {
     int32_t changed;     // a label changed in the last sweep
+    int32_t other;       // ... of the other direction (not read)
     int32_t roots;       // u's of this phase
     int32_t left[2];     // u's waiting for a scan (two lists used in turn)
 };
@@ -309,7 +318,7 @@ __global__ void repair_init_kernel(int32_t *m, int32_t *stamp, int32_t *holder, 
         stamp[i] = 0;
         holder[i] = kFree;
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) *c = RepairCounts{0, 0, {0, 0}};
+    if (blockIdx.x == 0 && threadIdx.x == 0) *c = RepairCounts{0, 0, 0, {0, 0}};
 }
 
 __global__ void repair_flag_kernel(int32_t *flag, int32_t v) { *flag = v; }
@@ -377,6 +386,53 @@ __global__ void __launch_bounds__(256) pull_labels_kernel(const int32_t *graph, 
     if (v < n && s == 0 && l < own) {
         m[v] = l;
         *changed = 1;
+    }
+}
+
+// start of joining: the other direction's labels and the joined nodes' roots
+__global__ void join_init_kernel(int32_t *other, int32_t *root, int64_t n, int32_t medoid)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) other[i] = root[i] = i == medoid ? -1 : (int32_t)i;
+}
+
+// Labels name nodes, -1 the medoid.  A node that is reached by the node it
+// reaches (both labels name it) lies on a cycle with it, and so do the roots:
+// the larger root gets the smaller one.  Every node and its root then share
+// their labels of both directions, so that a label that arrives at one node of
+// a joined set is everywhere in it two rounds later.  Whatever the threads see
+// of each other's writes, only nodes of one cycle are joined, and labels only
+// fall to labels of the same cycle.  m: the phase's labels, pushed: which of the
+// two goes by stamps (stamp `next` makes the next sweep offer a label).
+__global__ void __launch_bounds__(256) join_kernel(int32_t *m, int32_t *other, int32_t *root, int64_t n,
+                                                   int32_t medoid, const int32_t *pushed, int32_t *stamp,
+                                                   int next, int32_t *changed)
+{
+    const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (v >= n) return;
+    auto node = [&](int32_t k) { return k < 0 ? medoid : k; };
+    int32_t c = root[v];
+    const int32_t a = m[v];
+    if (a == other[v] && a != c) {
+        const int32_t lo = a < c ? a : c, hi = a < c ? c : a;
+        atomicMin(&root[node(hi)], lo);
+        c = lo;
+    }
+    const int32_t up = root[node(c)];
+    if (up < c) c = up;
+    if (c < root[v]) atomicMin(&root[v], c);
+    const int32_t r = node(c);
+    if (r == v) return;
+    for (int which = 0; which < 2; ++which) {
+        int32_t *l = which ? other : m;
+        const int32_t lv = l[v], lr = l[r];
+        if (lv == lr) continue;
+        const int32_t to = lv < lr ? lv : lr;
+        const int64_t w = lv < lr ? r : v;
+        if (atomicMin(&l[w], to) > to) {
+            if (l == pushed) stamp[w] = next;
+            if (l == m) *changed = 1;
+        }
     }
 }
 
@@ -712,13 +768,31 @@ ann_status repair_phase(const float *base, int64_t n, int dim, const int32_t *ca
                 hipLaunchKernelGGL(repair_flag_kernel, dim3(1), dim3(1), 0, st, &t.counts->changed, 0);
                 ANN_LAUNCHED();
             }
-            if (phase == 0)
+            const bool join = round >= LONG_SWEEPS;
+            // the lists for the scans are not in use yet
+            int32_t *other = t.list[0], *root = t.list[1], *pushed = phase == 0 ? t.m : other;
+            const int turn = phase == 0 ? round : round - LONG_SWEEPS;     // of the pushed labels
+            if (round == LONG_SWEEPS) {
+                hipLaunchKernelGGL(join_init_kernel, dim3(rows), dim3(256), 0, st, other, root, n, medoid);
+                ANN_LAUNCHED();
+            }
+            if (phase == 0 || join) {
                 hipLaunchKernelGGL(push_labels_kernel, dim3(sweep), dim3(256), 0, st, graph, n, R, lw,
-                                   t.m, t.stamp, round, &t.counts->changed);
-            else
+                                   pushed, t.stamp, turn,
+                                   phase == 0 ? &t.counts->changed : &t.counts->other);
+                ANN_LAUNCHED();
+            }
+            if (phase == 1 || join) {
                 hipLaunchKernelGGL(pull_labels_kernel, dim3(sweep), dim3(256), 0, st, graph, n, R, lw,
-                                   t.m, &t.counts->changed);
-            ANN_LAUNCHED();
+                                   phase == 1 ? t.m : other,
+                                   phase == 1 ? &t.counts->changed : &t.counts->other);
+                ANN_LAUNCHED();
+            }
+            if (join) {
+                hipLaunchKernelGGL(join_kernel, dim3(rows), dim3(256), 0, st, t.m, other, root, n, medoid,
+                                   pushed, t.stamp, turn + 1, &t.counts->changed);
+                ANN_LAUNCHED();
+            }
         }
         ann_status s = read_counts(t.counts, h, st);
         if (s != ANN_OK) return s;

@@ -445,19 +445,33 @@ def _repair_points(which):
     if which == "line":
         # points on a line, one candidate each: chains, and full scans for the rest
         return r.permutation(701)[:, None] * np.array([[1, 0, 0]]), 1, 3, 1.2
+    i = np.arange(3001)
+    if which == "line in order":
+        # the medoid's label has to travel 1,500 edges each way
+        return i[:, None] * np.array([[1, 0, 0, 0]]), 4, 4, 1.0
+    if which == "lines apart":
+        # ... in three lines, ids against, along and across the order
+        x = np.concatenate([i[:1000][::-1], i[:1000] + 20000, r.permutation(1001) + 60000])
+        return x[:, None] * np.array([[1, 0, 0, 0]]), 4, 4, 1.0
+    if which == "one way":
+        # spacings that grow: the candidates all lie on one side, so the
+        # edges do too
+        x = np.rint(np.cumsum(1.02 ** np.arange(700)))
+        return x[:, None] * np.array([[1, 0]]), 3, 4, 1.0
     # "ring": two candidates each, so labels travel along one long chain
     a = np.arange(1024) * (2 * np.pi / 1024)
     base = np.rint(np.stack([np.cos(a), np.sin(a), 0 * a, 0 * a], 1) * 4096)
     return base[r.permutation(1024)], 2, 4, 1.0
 
 
-@pytest.mark.parametrize("which", ["equal points", "islands", "line", "ring"])
+@pytest.mark.parametrize("which", ["equal points", "islands", "line", "ring", "line in order",
+                                   "lines apart", "one way"])
 def test_build_graph_repair_bit_exact(which):
     base, K, R, alpha = _repair_points(which)
     base = np.ascontiguousarray(base, np.float32)
     say("case: repair, %s" % which)
     ref, med, nf, nr, _, _ = oracle.build_graph(base, K, R, alpha)
-    assert nf > 0 or which == "ring"
+    assert nf > 0 or which in ("ring", "line in order", "one way")
     g, gm, (gf, gr) = _ann().ann_build_graph(_dev(base), K, R, alpha)
     torch.cuda.synchronize()
     assert gm == med and (gf, gr) == (nf, nr)
