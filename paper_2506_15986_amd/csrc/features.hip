@@ -79,12 +79,6 @@ __device__ inline double wmax(double v)
     for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o));
     return v;
 }
-__device__ inline int wsumi(int v)
-{
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    return v;
-}
-
 __device__ inline uint64_t dkey(double v)
 {
     return (uint64_t)__double_as_longlong(v);   // v >= 0: bit order = value order

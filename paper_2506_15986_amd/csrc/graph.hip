@@ -998,7 +998,7 @@ extern "C" ann_status ann_build_graph(const float *base, int64_t n, int32_t dim,
     // exact kNN candidates (self excluded), then pruning, medoid, repair
     ann_status s = knn_run(base, n, dim, base, n, K, true, cand, nullptr, cd2, knn_ws, kws, st, 0);
     if (s != ANN_OK) return s;
-    return graph_tail(base, n, dim, cand, cd2, K, R, alpha, graph, medoid, bridges, t, st);
+    return no_throw([&] { return graph_tail(base, n, dim, cand, cd2, K, R, alpha, graph, medoid, bridges, t, st); });
 }
 
 namespace {
@@ -1134,14 +1134,16 @@ extern "C" ann_status ann_group_candidates(const float *base, int64_t n, int32_t
     ANN_REQUIRE(g_begin >= 0 && g_begin <= g_end && g_end <= n_groups,
                 "group range must satisfy 0 <= g_begin <= g_end <= n_groups");
     hipStream_t st = static_cast<hipStream_t>(stream);
-    GroupLists L;
-    ann_status s = group_lists(groups, n, n_member, n_groups, st, L);
-    if (s != ANN_OK) return s;
-    ANN_REQUIRE(ws_bytes >= group_cand_accepts(dim, knn_k, L.max_mem, L.max_home),
-                "workspace too small (largest member set %lld, largest home set %lld)",
-                (long long)L.max_mem, (long long)L.max_home);
-    Carve cv{static_cast<unsigned char *>(workspace)};
-    return group_candidates(base, dim, knn_k, L, g_begin, g_end, cand, cand_d2, cv, ws_bytes, st);
+    return no_throw([&]() -> ann_status {
+        GroupLists L;
+        ann_status s = group_lists(groups, n, n_member, n_groups, st, L);
+        if (s != ANN_OK) return s;
+        ANN_REQUIRE(ws_bytes >= group_cand_accepts(dim, knn_k, L.max_mem, L.max_home),
+                    "workspace too small (largest member set %lld, largest home set %lld)",
+                    (long long)L.max_mem, (long long)L.max_home);
+        Carve cv{static_cast<unsigned char *>(workspace)};
+        return group_candidates(base, dim, knn_k, L, g_begin, g_end, cand, cand_d2, cv, ws_bytes, st);
+    });
 }
 
 extern "C" size_t ann_graph_from_candidates_workspace_size(int64_t n, int32_t dim, int32_t R)
@@ -1170,7 +1172,7 @@ extern "C" ann_status ann_graph_from_candidates(const float *base, int64_t n, in
     hipStream_t st = static_cast<hipStream_t>(stream);
     Carve cv{static_cast<unsigned char *>(workspace)};
     TailBufs t = take_tail(cv, n, dim);
-    return graph_tail(base, n, dim, cand, cand_d2, knn_k, R, alpha, graph, medoid, bridges, t, st);
+    return no_throw([&] { return graph_tail(base, n, dim, cand, cand_d2, knn_k, R, alpha, graph, medoid, bridges, t, st); });
 }
 
 extern "C" size_t ann_build_graph_partitioned_workspace_size(int64_t n, int32_t dim,
@@ -1196,23 +1198,25 @@ extern "C" ann_status ann_build_graph_partitioned(const float *base, int64_t n, 
     ANN_REQUIRE(knn_k >= R - 2, "knn_k must be >= R-2");
     ANN_REQUIRE(alpha >= 1.0f, "alpha must be >= 1");
     hipStream_t st = static_cast<hipStream_t>(stream);
-    GroupLists L;
-    ann_status s = group_lists(groups, n, n_member, n_groups, st, L);
-    if (s != ANN_OK) return s;
-    const size_t lists = round_up((size_t)n * knn_k * 4, 256) + round_up((size_t)n * knn_k * 8, 256);
-    ANN_REQUIRE(ws_bytes >= lists + std::max(tail_ws(n, dim, R),
-                                             group_cand_accepts(dim, knn_k, L.max_mem, L.max_home)),
-                "workspace too small (largest member set %lld, largest home set %lld)",
-                (long long)L.max_mem, (long long)L.max_home);
-    const int K = knn_k;
-    Carve cv{static_cast<unsigned char *>(workspace)};
-    int32_t *cand = cv.take<int32_t>((size_t)n * K);
-    double *cd2 = cv.take<double>((size_t)n * K);
-    // the kNN staging and the tail's buffers share what is left
-    s = group_candidates(base, dim, K, L, 0, n_groups, cand, cd2, cv, ws_bytes - lists, st);
-    if (s != ANN_OK) return s;
-    TailBufs t = take_tail(cv, n, dim);
-    return graph_tail(base, n, dim, cand, cd2, K, R, alpha, graph, medoid, bridges, t, st);
+    return no_throw([&]() -> ann_status {
+        GroupLists L;
+        ann_status s = group_lists(groups, n, n_member, n_groups, st, L);
+        if (s != ANN_OK) return s;
+        const size_t lists = round_up((size_t)n * knn_k * 4, 256) + round_up((size_t)n * knn_k * 8, 256);
+        ANN_REQUIRE(ws_bytes >= lists + std::max(tail_ws(n, dim, R),
+                                                 group_cand_accepts(dim, knn_k, L.max_mem, L.max_home)),
+                    "workspace too small (largest member set %lld, largest home set %lld)",
+                    (long long)L.max_mem, (long long)L.max_home);
+        const int K = knn_k;
+        Carve cv{static_cast<unsigned char *>(workspace)};
+        int32_t *cand = cv.take<int32_t>((size_t)n * K);
+        double *cd2 = cv.take<double>((size_t)n * K);
+        // the kNN staging and the tail's buffers share what is left
+        s = group_candidates(base, dim, K, L, 0, n_groups, cand, cd2, cv, ws_bytes - lists, st);
+        if (s != ANN_OK) return s;
+        TailBufs t = take_tail(cv, n, dim);
+        return graph_tail(base, n, dim, cand, cd2, K, R, alpha, graph, medoid, bridges, t, st);
+    });
 }
 
 extern "C" ann_status ann_medoid(const float *base, int64_t n, int32_t dim, int32_t *medoid,

@@ -1,9 +1,25 @@
 // Internal cross-file declarations of libann (sizes of composite workspaces).
 #pragma once
 
+#include <new>
+#include <stdexcept>
+
 #include "common.h"
 
 namespace ann {
+
+// Host memory that runs out inside an entry point is a status, not an
+// exception across the C ABI.
+template <class F> ann_status no_throw(F f)
+{
+    try {
+        return f();
+    } catch (const std::bad_alloc &) {
+        return fail(ANN_ENOMEM, "out of host memory");
+    } catch (const std::length_error &) {
+        return fail(ANN_ENOMEM, "out of host memory");
+    }
+}
 
 struct Carve {
     unsigned char *p;

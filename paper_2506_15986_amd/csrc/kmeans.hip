@@ -1666,8 +1666,10 @@ extern "C" ann_status ann_select_hubs_hbkm(const float *base, int64_t n, int32_t
     ANN_REQUIRE(lambda >= 0.0 && lambda < 1e300, "lambda must be finite and >= 0");
     ANN_REQUIRE(iters >= 1, "iters must be >= 1");
     ANN_REQUIRE(ws_bytes >= hbkm_ws(n, dim, k, levels), "workspace too small");
-    return hbkm_run(base, n, dim, k, levels, lambda, iters, hub_ids, centroids, assign, workspace,
-                    static_cast<hipStream_t>(stream));
+    return no_throw([&] {
+        return hbkm_run(base, n, dim, k, levels, lambda, iters, hub_ids, centroids, assign, workspace,
+                        static_cast<hipStream_t>(stream));
+    });
 }
 
 extern "C" ann_status ann_select_hubs(const float *base, int64_t n, int32_t dim, int32_t n_hubs,
@@ -1682,8 +1684,10 @@ extern "C" ann_status ann_select_hubs(const float *base, int64_t n, int32_t dim,
     ANN_REQUIRE(iters >= 1, "iters must be >= 1");
     ANN_REQUIRE(ws_bytes >= ann_workspace_size(ANN_OP_SELECT_HUBS, n, dim, n_hubs, 0),
                 "workspace too small");
-    return select_hubs_run(base, n, dim, n_hubs, iters, init_ids, hub_ids, centroids, assign, steps,
-                           workspace, static_cast<hipStream_t>(stream));
+    return no_throw([&] {
+        return select_hubs_run(base, n, dim, n_hubs, iters, init_ids, hub_ids, centroids, assign, steps,
+                               workspace, static_cast<hipStream_t>(stream));
+    });
 }
 
 // Seeded k-means start.  The generator is SplitMix64 (Steele, Lea and Flood,
@@ -1697,20 +1701,22 @@ extern "C" ann_status ann_hub_init_ids(int64_t n, int32_t n_hubs, uint64_t seed,
     ANN_REQUIRE(ids != nullptr, "ids is NULL");
     ANN_REQUIRE(n >= 1 && n <= 0x7FFFFFFF, "n must be in [1, 2^31)");
     ANN_REQUIRE(n_hubs >= 1 && n_hubs <= n, "n_hubs must be in [1, n]");
-    std::unordered_set<int64_t> taken;
-    taken.reserve((size_t)n_hubs * 2);
-    uint64_t state = seed;
-    int32_t i = 0;
-    for (int64_t j = n - n_hubs; j < n; ++j) {
-        state += 0x9E3779B97F4A7C15ull;
-        uint64_t z = state;
-        z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
-        z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
-        z ^= z >> 31;
-        const int64_t t = (int64_t)(((unsigned __int128)z * (uint64_t)(j + 1)) >> 64);
-        const int64_t v = taken.count(t) ? j : t;
-        taken.insert(v);
-        ids[i++] = (int32_t)v;
-    }
-    return ANN_OK;
+    return no_throw([&]() -> ann_status {
+        std::unordered_set<int64_t> taken;
+        taken.reserve((size_t)n_hubs * 2);
+        uint64_t state = seed;
+        int32_t i = 0;
+        for (int64_t j = n - n_hubs; j < n; ++j) {
+            state += 0x9E3779B97F4A7C15ull;
+            uint64_t z = state;
+            z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+            z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+            z ^= z >> 31;
+            const int64_t t = (int64_t)(((unsigned __int128)z * (uint64_t)(j + 1)) >> 64);
+            const int64_t v = taken.count(t) ? j : t;
+            taken.insert(v);
+            ids[i++] = (int32_t)v;
+        }
+        return ANN_OK;
+    });
 }

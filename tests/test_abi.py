@@ -177,6 +177,20 @@ raise SystemExit(1)
     assert p.returncode == 0, (p.returncode, p.stderr[-400:])
 
 
+def test_host_memory_that_runs_out_is_a_status(lib):
+    # no exception crosses the ABI: a table of 2^32 buckets under a limit of
+    # 16 GiB of address space (refused before the ids are written)
+    code = """
+import ctypes, resource
+from paper_2506_15986_amd import ann
+resource.setrlimit(resource.RLIMIT_AS, (16 << 30, 16 << 30))
+s = ann._lib.ann_hub_init_ids(ctypes.c_int64(2 ** 31 - 1), 2 ** 31 - 1, ctypes.c_uint64(0), ctypes.c_void_p(0x10000))
+raise SystemExit(0 if s == ann.ANN_ENOMEM else 1)
+"""
+    p = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=120)
+    assert p.returncode == 0, (p.returncode, p.stderr[-400:])
+
+
 def test_kernel_names_unique_across_translation_units():
     # each .hip file is its own code object inside libann.so; two code objects
     # exporting the same kernel symbol must not happen
