@@ -925,7 +925,7 @@ __global__ void __launch_bounds__(256) cluster_sum_kernel(const float *base, int
 }
 
 // one wavefront per point, one atomic per dimension: for clusters too many for
-// the sort's counters in LDS
+// the sort's counters in LDS, and for few values
 __global__ void accumulate_kernel(const float *base, int64_t n, int dim, const int32_t *assign,
                                   double *sums, int64_t *count)
 {
@@ -1363,8 +1363,20 @@ ann_status select_hubs_run(const float *base, int64_t n, int dim, int nh, int it
     // the matrix-core assignments need whole float4 rows
     const bool mfma = dim % 4 == 0 && aligned(base, 16);
     const bool vec4 = mfma && aligned(mu, 16);
-    const int padded = mfma ? half_padded(dim, nh) : 0;
-    const bool sort = nh <= SORT_MAX_NH;
+    // few products, of short rows with few centroids (which a workgroup of the
+    // FP32 kernel goes through one after the other): one launch of that instead
+    // of the four that the FP16 products and what they leave open take.  us a step,
+    // FP32 / FP16: 1,000 points x 64 centroids x 16 dimensions 51 / 79, 16,384 x
+    // 128 x 128 96 / 113; but 16,384 x 512 x 32 103 / 94, 4,096 x 500 x 128 151 / 106,
+    // and beyond 2^28 products FP16 is ahead with any number.
+    const bool few = dim <= 128 && nh <= 256 && nh * dim <= (1 << 14) &&
+                     n * nh * (int64_t)dim <= (1 << 28);
+    const int padded = mfma && !few ? half_padded(dim, nh) : 0;
+    // few values, and few of them on one address: the atomics cost less than the
+    // two launches more that the sort takes (us a step at 256 clusters: 2,000 x
+    // 16 78 / 86, 1,000 x 64 93 / 99; with more than 64 points on an address the sort
+    // is ahead: 1,000 x 15, 8 clusters 60 / 56)
+    const bool sort = nh <= SORT_MAX_NH && ((int64_t)n * dim > (1 << 18) || n > 64 * (int64_t)nh);
     ShortArgs sa{};
     HalfArgs ha{};
     CentroidArgs ca{};

@@ -155,13 +155,29 @@ def test_hub_features_match_oracle():
     assert np.allclose(f.cpu().numpy(), ref, rtol=0, atol=1e-4)
 
 
+@pytest.mark.parametrize("case,n,dim,nh,iters", [
+    ("ints", 5000, 20, 900, 4),        # the FP16 products, one fragment, part of it
+    ("ints", 5000, 64, 300, 5),        # two
+    ("offset", 4000, 96, 200, 5),      # three, far from the origin
+    ("outlier", 4000, 128, 150, 5),    # four; a point beyond FP16's range
+    ("tight", 140000, 32, 64, 3),      # more points left than the class search takes
+    ("ints", 3000, 64, 256, 4),        # the last shape of the FP32 kernel alone
+    ("ints", 3000, 64, 257, 4),        # ... and the first past it
+    ("ints", 6400, 8, 100, 4),         # sums by atomics: 64 points a cluster,
+    ("ints", 6401, 8, 100, 4),         # by the sort: more
+])
+def test_select_hubs_dispatch_lines(case, n, dim, nh, iters):
+    test_select_hubs_bit_exact_assignment_paths(case, n, dim, nh, iters)
+
+
 @pytest.mark.parametrize("m", [2, 3, 4, 5])
 def test_select_hubs_equal_centroids(m):
     # every centroid starts m times over, in lanes of their own: a point has m
     # open candidates (up to four are decided in one list, five go to the
     # class search) and takes the first
     r = np.random.default_rng(m)
-    n, dim, places = 4000, 64, 12
+    # (more than 16,384 centroid values: the FP16 products)
+    n, dim, places = 4000, 64, 140
     base = r.integers(0, 256, size=(n, dim)).astype(np.float32)
     init = r.choice(n, m * places, replace=False).astype(np.int32)
     for j in range(m):
