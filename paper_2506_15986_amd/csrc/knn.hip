@@ -996,9 +996,15 @@ size_t knn_workspace(int64_t n, int64_t rows, int dim, int K)
 
 // rows of a batch of the FP16 shortlist in `bytes` of memory; 0: too little, the
 // plain engine's turn
+//
+// Few rows against few columns go through the plain engine's one launch: the
+// shortlist's ten take 80 us (1 row, 10 nearest of 200 x 31 in 49 us, of 64 x 260
+// in 65; 8 rows of 64 x 31 in 73; but 1 of 200 x 129 in 118, 16 rows of 64 x 8
+// in 124).
 static int64_t real_batch(int64_t n, int64_t rows, int dim, int K, size_t bytes)
 {
     if (dim > (1 << 20)) return 0;   // a workgroup's 256 rows stay below 2 GiB (buffer offsets)
+    if (rows <= 8 && n <= 512 && n * (dim + 64) <= 26000 - 2300 * rows) return 0;
     auto fits = [&](int64_t b) { return real_bytes(n, rows, b, dim, K) <= bytes; };
     if (rows <= f16::kMostRows && fits(rows)) return rows;
     const int64_t round = 2 * (int64_t)device_cus() * f16::kRowsWG;

@@ -296,6 +296,14 @@ def test_real_valued_second_level_matches_oracle(n, nq, d, k, kind):
     test_real_valued_knn_matches_oracle(n, nq, d, k, kind)
 
 
+@pytest.mark.parametrize("n,nq,d,k", [
+    (249, 1, 31, 10), (250, 1, 31, 10),    # the last shape of the plain engine, the first of the shortlist
+    (109, 8, 6, 64), (110, 8, 6, 64), (109, 9, 6, 64), (64, 1, 300, 3), (1, 1, 1, 1), (3, 8, 5, 7),
+])
+def test_real_valued_knn_of_few_rows(n, nq, d, k):
+    test_real_valued_knn_matches_oracle(n, nq, d, k, "normal")
+
+
 @pytest.mark.parametrize("exclude", [False, True])
 @pytest.mark.parametrize("n,d,k,kind", [(16_385, 20, 30, "normal"), (16_384, 33, 16, "tight"),
                                         (20_011, 36, 20, "copies"), (20_011, 100, 64, "tight")])
