@@ -328,7 +328,7 @@ __device__ inline int sort_keep(uint64_t *g, int c, int Kp, uint64_t *s, int32_t
 
 // One wave: drop entries of g that cannot be among the best Kp.  Finds by
 // bisection a d2 bound T that at least Kp and if possible at most Kp + slack of
-// the c entries (all <= top) meet, and keeps those, in no particular order;
+// the c entries (of which Kp are <= top) meet, and keeps those, in no order;
 // returns their count and sets thr to T.  c >= Kp, c <= 64 E.  A sort of 256
 // entries by exchanges in LDS took 36 passes where this takes about ten counts
 // of registers.
@@ -582,9 +582,12 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KS <= 
             // d2 <= thr  <=>  2 dot + nbc > r_tv.  With nbc = 2 half + odd and
             // acc = dot + half that is 2 acc + odd > r_tv, which implies
             // acc > floor((r_tv - 1) / 2): one compare per distance, one ballot
-            // for the 16 of this lane, and the odd bit is looked at for those
-            // that pass.  An equal d2 is let in (the sort orders ties by id),
-            // so the columns may come in any order.
+            // for the 16 of this lane.  It lets in some d2 = thr + 1 too, which a
+            // later cut drops (to look at the odd bit cost more: 40,000 x 32 with
+            // itself, K = 1,000, where most columns pass, 114 ms, 110 now; 300,000 x 128, K = 128, the whole build
+            // 32.9 and 30.8).  An
+            // equal d2 is let in (the sort orders ties by id), so the columns may
+            // come in any order.
             // (The largest difference, not sixteen compares: those put their
             // results where the scalar unit waits for each.)
             int32_t most = -0x7fffffff;
@@ -610,15 +613,12 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KS <= 
                 for (int rb = 0; rb < 4; ++rb)
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        const bool near = acc[rb][i] > tv[rb][i];
-                        if (!__builtin_amdgcn_ballot_w64(near)) continue;
-                        const int rl = rq + 16 * rb + i;
-                        const int32_t v = 2 * acc[rb][i] + (nbc & 1);
-                        const bool in = near && v > r_tv[rl];
+                        const bool in = acc[rb][i] > tv[rb][i];
                         const uint64_t m = __builtin_amdgcn_ballot_w64(in);
                         if (!m) continue;
                         if (in) {
-                            const int32_t d2 = r_an[rl] - v;
+                            const int rl = rq + 16 * rb + i;
+                            const int32_t d2 = r_an[rl] - 2 * acc[rb][i] - (nbc & 1);
                             const int slot = atomicAdd(&r_cnt[rl], 1);
                             const uint64_t word = ((uint64_t)(uint32_t)d2 << 32) |
                                                   (uint32_t)Bid[cur * kCols + 16 * cb + (sl & 15)];
