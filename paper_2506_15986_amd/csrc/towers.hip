@@ -158,15 +158,20 @@ struct FStage {
     }
 };
 
-// two products in one launch: blockIdx.z picks (`two` is 1 then, else 0); a
-// launch holds 65,535 workgroups in y, further rows follow in z
-__global__ void __launch_bounds__(256) gemm_f32_kernel(GemmF g0, GemmF g1, int two)
+// Two products in one launch: the lowest bit of blockIdx.z picks.  A launch
+// holds 65,535 workgroups in y; TALL: further rows follow in z.
+template <bool TALL>
+__global__ void __launch_bounds__(256) gemm_f32_kernel(GemmF g0, GemmF g1)
 {
-    const GemmF &g = blockIdx.z & two ? g1 : g0;
-    const int64_t row = (int64_t)((blockIdx.z >> two) * gridDim.y + blockIdx.y) * FM;
+    const GemmF &g = blockIdx.z & 1u ? g1 : g0;
     const int n0 = (int)blockIdx.x * FN;
-    if (row >= g.M || n0 >= g.N) return;
-    const int m0 = (int)row;
+    int m0 = (int)blockIdx.y * FM;
+    if (TALL) {
+        const int64_t row = ((int64_t)(blockIdx.z >> 1) * gridDim.y + blockIdx.y) * FM;
+        if (row >= g.M) return;
+        m0 = (int)row;
+    }
+    if (m0 >= g.M || n0 >= g.N) return;
     __shared__ __align__(16) float As[FM * FS], Bs[FN * FS];
     const int t = threadIdx.x, lane = t & 63;
     const int w = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -764,10 +769,12 @@ ann_status gemm_f32(const GemmF &g, const GemmF *h, hipStream_t st)
 {
     const GemmF &g1 = h ? *h : g;
     const int M = g.M > g1.M ? g.M : g1.M, N = g.N > g1.N ? g.N : g1.N;
-    const unsigned my = ((unsigned)M + FM - 1) / FM, two = h ? 1u : 0u;
-    const unsigned ny = my < 65535u ? my : 65535u;
-    hipLaunchKernelGGL(gemm_f32_kernel, dim3((unsigned)((N + FN - 1) / FN), ny, ((my + ny - 1) / ny) << two),
-                       dim3(256), 0, st, g, g1, (int)two);
+    const unsigned nx = (unsigned)((N + FN - 1) / FN), my = ((unsigned)M + FM - 1) / FM;
+    if (my <= 65535u)
+        hipLaunchKernelGGL(gemm_f32_kernel<false>, dim3(nx, my, h ? 2 : 1), dim3(256), 0, st, g, g1);
+    else    // (one product: the second of each pair of layers, an empty one)
+        hipLaunchKernelGGL(gemm_f32_kernel<true>, dim3(nx, 65535u, 2 * ((my + 65534u) / 65535u)), dim3(256), 0,
+                           st, g, h ? g1 : GemmF{});
     ANN_LAUNCHED();
     return ANN_OK;
 }
