@@ -243,8 +243,8 @@ struct FeatArgs {
 // What bounds it: the chain of batches (graph row, neighbour rows, sort, set)
 // of a hub, about 5 us each; sixteen nodes at a time make it as many times
 // shorter, and the hubs' chains run side by side.  200,000 x 128, 1,024 hubs:
-// 22.7 ms with one wavefront per hub and a bitmap in memory, 4.4 ms now (the whole
-// call 24.2 and 4.7).
+// 22.7 ms with one wavefront per hub and a bitmap in memory, 4.2 ms now (the whole
+// call 24.2 and 4.6).
 __global__ void __launch_bounds__(64 * FW_WAVES) walk_kernel(FeatArgs a)
 {
     extern __shared__ __align__(16) unsigned char lds[];

@@ -243,9 +243,9 @@ __global__ void __launch_bounds__(256) knn_f64_kernel(KnnArgs a)
 // asked, and writes the K best.
 //
 // Bound by the tiles' arrival (a column tile is requested one tile ahead) and
-// the tests beside the products: 1,000,000 x 128 with itself, K = 64, 152 ms
-// (1,690 TOP/s; 198 with the bounds in LDS, a compare per distance and sorts
-// for cuts); 300,000 x 128, K = 128, 24 ms (43; the products and tests alone
+// the tests beside the products: 1,000,000 x 128 with itself, K = 128, 156 ms
+// (1,644 TOP/s; 220 with the bounds in LDS, a compare per distance and sorts
+// for cuts); 300,000 x 128, K = 128, 22 ms (43; the products and tests alone
 // 15).
 namespace i8 {
 
@@ -584,10 +584,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KS <= 
             // acc > floor((r_tv - 1) / 2): one compare per distance, one ballot
             // for the 16 of this lane.  It lets in some d2 = thr + 1 too, which a
             // later cut drops (to look at the odd bit cost more: 40,000 x 32 with
-            // itself, K = 1,000, where most columns pass, 114 ms, 110 now; 300,000 x 128, K = 128, the whole build
-            // 32.9 and 30.8).  An
-            // equal d2 is let in (the sort orders ties by id), so the columns may
-            // come in any order.
+            // itself, K = 1,000, where most columns pass, 114 ms, 110 now; the
+            // build of 300,000 x 128, K = 128, 32.9 and 30.6).  An equal d2 is let in
+            // (the sort orders ties by id), so the columns may come in any order.
             // (The largest difference, not sixteen compares: those put their
             // results where the scalar unit waits for each.)
             int32_t most = -0x7fffffff;

